@@ -85,8 +85,11 @@ typedef struct {
                           whose sub-step chains set the launch's time) and sixteen for the rest
                           (needs the workspace, which holds the order; as 2 without it);
                           automatic takes 5 where the reaction slots divide in two, else 16 lanes,
-                          where compiled, else one cell per lane, else a wavefront.  Mappings 2, 4
-                          and 5 give the same bits */
+                          where compiled, else one cell per lane, else a wavefront.  Where a
+                          mechanism's rates fit the lanes of one wave (up to 31 reactions, four spare
+                          lanes per falloff reaction), automatic, 2, 4 and 5 and the queue
+                          schedule all run one wavefront per cell with tables in registers.
+                          Automatic, 2, 4 and 5 give the same bits */
     int32_t schedule;  /* 0 (default) or 1: static, one launch that gives each lane (or group of
                           16 lanes) one cell; 2: persistent work queue (needs the workspace):
                           cells sorted by estimated cost (temperature, then step length) are

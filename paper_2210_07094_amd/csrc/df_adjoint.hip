@@ -668,7 +668,10 @@ extern "C" df_status df_chem_step_taped(const df_mech *mech, int64_t n_cells, in
     StepArgs a{n_cells, ld, dt, nullptr, p, T, Y, nullptr, nullptr, cell_status, n_steps, kernel_opts(o), DF_CELL_OK};
     a.tape = static_cast<double *>(tape);
     a.tape_cap = max_substeps;
-    return launch_chem_coop(mech->dev, a, CellQueue{nullptr, nullptr, nullptr, nullptr, nullptr, 0},
+    const auto launch = chem_cell_supported(mech->dev) ? launch_chem_cell
+                                                       : [](const MechDev &m, const StepArgs &s, const CellQueue &q,
+                                                            hipStream_t st) { return launch_chem_coop(m, s, q, st); };
+    return launch(mech->dev, a, CellQueue{nullptr, nullptr, nullptr, nullptr, nullptr, 0},
                             static_cast<hipStream_t>(hip_stream));
 }
 

@@ -55,11 +55,14 @@ static df_status launch_k(const MechDev &m, const StepArgs &a, const int32_t *ci
 df_status launch_chem_step(const MechDev &m, const StepArgs &a, int mapping, const int32_t *cidx,
                            const int32_t *dcount, hipStream_t stream) {
     if (a.n == 0) return DF_OK;
-    // mapping 0 picks 16 lanes per cell whenever a kernel is compiled for K: one sub-step
-    // then takes a fraction of the latency, which bounds a stiff cell's step time; with the cost
-    // order (and reaction slots that divide in two) the head of the order takes 32 lanes, the
-    // head variant (mapping 5), whose stiffest cells then finish sooner
+    // one wave per cell wherever the mechanism's rates fit a wave's lanes (mappings 0, 2, 4 and 5): a
+    // sub-step, whose latency bounds a stiff cell, takes 18k cycles there against 40 to 47k at 16 or 32
+    // lanes.  Larger mechanisms: mapping 0 picks 16 lanes per cell whenever a kernel is compiled for
+    // K, and with the cost order (and reaction slots that divide in two) 32 lanes for the head of
+    // the order (mapping 5), whose stiffest cells then finish sooner
     if (mapping == 3) return launch_chem_wave(m, a, cidx, dcount, stream);
+    if (mapping != 1 && chem_cell_supported(m))
+        return launch_chem_cell(m, a, CellQueue{cidx, dcount, nullptr, nullptr, nullptr, 0}, stream);
     if (mapping == 2 || mapping == 4 || mapping == 5 || (mapping == 0 && chem_coop_supported(m)))
         return launch_chem_coop(m, a, CellQueue{cidx, dcount, nullptr, nullptr, nullptr, 0}, stream,
                                 mapping == 4 ? 2 : (mapping == 5 || mapping == 0 ? 3 : 1));
@@ -82,7 +85,7 @@ namespace {
 constexpr int kTB = 256, kDB = 16;      // temperature and step-length buckets
 constexpr int kBuckets = kTB * kDB;     // bucket = tb * kDB + db; bucket 0 = hottest, longest step
 constexpr double kTlo = 200.0, kThi = 3500.0;
-constexpr int kOrdThreads = 256;
+constexpr int kOrdThreads = 1024;
 // cells of the buckets at or below about this temperature form the cold tail of the queue,
 // the only cells one-cell-per-lane waves take (they need about one sub-step each)
 constexpr double kTcold = 500.0;
@@ -148,6 +151,9 @@ __global__ __launch_bounds__(kOrdThreads) void order_scan(int32_t *cnt) {
         cnt[kBuckets + t * R + q] = base;
         base += cnt[t * R + q];
     }
+    // the counts are used up: their first kilobyte becomes the per-group counters of the cell queue
+    __syncthreads();
+    if (t < kCellQueues * 32) cnt[t] = 0;
 }
 
 __global__ __launch_bounds__(kOrdThreads) void order_scatter(const double *__restrict__ T,
@@ -169,6 +175,83 @@ __global__ __launch_bounds__(kOrdThreads) void order_scatter(const double *__res
     if (i < n) idx[base[b] + rank] = int32_t(i);
 }
 
+// The whole sort in one block, for at most kOneBlockCells cells: the four dependent launches above take
+// about 18 us whatever the count, one block about 8 us for a thousand cells but 150 us for 65,536 (the
+// time is its serial rounds of LDS atomics), so the line lies where the two meet.
+// Neighbouring cells often share a bucket (a cold background): the lanes of a wave that agree with its
+// first lane make one LDS atomic together.
+constexpr int kOneThreads = 1024;
+constexpr int64_t kOneBlockCells = 4096;
+
+__device__ __forceinline__ int take_rank(int32_t *loc, int b) {
+    const int first = __builtin_amdgcn_readfirstlane(b);
+    const unsigned long long same = __builtin_amdgcn_ballot_w64(b == first);
+    const int lane = int(threadIdx.x) & 63;
+    int base = 0;
+    if (b == first) {
+        const int before = __popcll(same & ((1ull << lane) - 1ull));
+        if (before == 0) base = atomicAdd(&loc[b], __popcll(same));
+        return __builtin_amdgcn_readfirstlane(base) + before;
+    }
+    return atomicAdd(&loc[b], 1);
+}
+
+__global__ __launch_bounds__(kOneThreads) void order_one(const double *__restrict__ T, const double *__restrict__ dts,
+                                                         double dt, int n, int32_t *__restrict__ cnt,
+                                                         int32_t *__restrict__ tail,
+                                                         unsigned long long *__restrict__ ctr,
+                                                         int32_t *__restrict__ idx) {
+    constexpr int R = kBuckets / kOneThreads, U = 8;
+    __shared__ int32_t loc[kBuckets], sum[kOneThreads];
+    const int t = threadIdx.x;
+    for (int b = t; b < kBuckets; b += kOneThreads) loc[b] = 0;
+    __syncthreads();
+    auto pass = [&](auto &&use) {
+        for (int i0 = t; i0 < n; i0 += U * kOneThreads) {
+            double Tv[U], dv[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int i = i0 + u * kOneThreads;
+                Tv[u] = i < n ? T[i] : 0.0;
+                dv[u] = dts && i < n ? dts[i] : dt;
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int i = i0 + u * kOneThreads;
+                if (i < n) use(i, t_bucket(Tv[u]) * kDB + d_bucket(dv[u]));
+            }
+        }
+    };
+    pass([&](int, int b) { (void)take_rank(loc, b); });
+    __syncthreads();
+    int32_t run = 0, c[R];
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+        c[q] = loc[t * R + q];
+        run += c[q];
+    }
+    sum[t] = run;
+    __syncthreads();
+    for (int off = 1; off < kOneThreads; off <<= 1) {
+        const int32_t add = (t >= off) ? sum[t - off] : 0;
+        __syncthreads();
+        sum[t] += add;
+        __syncthreads();
+    }
+    int32_t base = sum[t] - run;
+    const int bcold = t_bucket(kTcold) * kDB;
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+        if (t * R + q == bcold) *tail = n - base;
+        loc[t * R + q] = base;
+        base += c[q];
+    }
+    if (t == 0) *ctr = 0ull;
+    if (t < kCellQueues * 32) cnt[t] = 0;
+    __syncthreads();
+    pass([&](int i, int b) { idx[take_rank(loc, b)] = int32_t(i); });
+}
+
 constexpr size_t al256(size_t x) { return (x + 255) & ~size_t(255); }
 
 // workspace: bucket counts and offsets | queue counter | cell order
@@ -180,17 +263,26 @@ struct Work {
     unsigned long long *ctr;
     int32_t *idx;
     int32_t *tail;  // cells in the cold buckets
+    unsigned long long *groups;  // counters of the cell queue, in the counts that the ordering has used up
 };
 
 Work work_parts(void *ws) {
     auto *b = static_cast<unsigned char *>(ws);
     auto *cnt = reinterpret_cast<int32_t *>(b);
     return Work{cnt, reinterpret_cast<unsigned long long *>(b + al256(kCntBytes)),
-                reinterpret_cast<int32_t *>(b + al256(kCntBytes) + 256), cnt + 2 * kBuckets};
+                reinterpret_cast<int32_t *>(b + al256(kCntBytes) + 256), cnt + 2 * kBuckets,
+                reinterpret_cast<unsigned long long *>(b)};
 }
 
 // cells in order of decreasing estimated cost into w.idx; zeroes the queue counter
 df_status order_cells(const StepArgs &a, const Work &w, hipStream_t s) {
+    if (a.n <= kOneBlockCells) {
+        hipLaunchKernelGGL(order_one, dim3(1), dim3(kOneThreads), 0, s, a.T, a.dts, a.dt, int(a.n), w.cnt, w.tail,
+                           w.ctr, w.idx);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return fail(DF_E_HIP, std::string("df_chem_step ordering: ") + hipGetErrorString(e));
+        return DF_OK;
+    }
     const unsigned blocks = unsigned((a.n + kOrdThreads - 1) / kOrdThreads);
     hipLaunchKernelGGL(order_zero, dim3(1), dim3(kOrdThreads), 0, s, w.cnt, w.ctr);
     hipLaunchKernelGGL(order_hist, dim3(blocks), dim3(kOrdThreads), 0, s, a.T, a.dts, a.dt, a.n, w.cnt);
@@ -227,10 +319,12 @@ df_status chem_step_impl(const char *who, const df_mech *mech, int64_t n_cells, 
         return fail(DF_E_HIP, w + ": cannot select the mechanism's device");
     auto s = static_cast<hipStream_t>(hip_stream);
     const StepArgs a{n_cells, ld, dt, dts, p, T, Y, h_inout, rr, cell_status, n_steps, kernel_opts(o), DF_CELL_OK};
-    const Work wk = workspace ? work_parts(workspace) : Work{nullptr, nullptr, nullptr, nullptr};
+    const Work wk = workspace ? work_parts(workspace) : Work{nullptr, nullptr, nullptr, nullptr, nullptr};
     if (workspace) st = order_cells(a, wk, s);
     if (st == DF_OK) {
-        if (o.schedule == 2) {
+        if (workspace && chem_cell_supported(mech->dev) && (o.schedule == 2 || (o.mapping != 1 && o.mapping != 3))) {
+            st = launch_chem_cell(mech->dev, a, CellQueue{nullptr, nullptr, wk.idx, wk.groups, nullptr, 0}, s);
+        } else if (o.schedule == 2) {
             const int32_t cap = chem_queue_capacity(mech->dev);
             int32_t head = o.coop_blocks == 0 ? cap : (o.coop_blocks < 0 ? 0 : o.coop_blocks);
             head = head > cap ? cap : head;
@@ -384,12 +478,14 @@ extern "C" df_status df_chem_autotune(const df_mech *mech, int64_t n_cells, int6
     void *ows = base;
     auto *Tc = reinterpret_cast<double *>(base + order_bytes(n_cells));
     auto *Yc = reinterpret_cast<double *>(base + order_bytes(n_cells) + al256(size_t(n_cells) * 8));
-    const int32_t cap = chem_queue_capacity(mech->dev);
+    // with one wave per cell every queue schedule and the 16- and 32-lane mappings are the same launch
+    const bool cell = chem_cell_supported(mech->dev);
+    const int32_t cap = cell ? 0 : chem_queue_capacity(mech->dev);
     struct Cand {
         int32_t schedule, coop_blocks, mapping;
     };
     std::vector<Cand> cands = {{1, 0, opts->mapping}};
-    if (chem_coop_supported(mech->dev) && mech->dev.RPL % 2 == 0 && (opts->mapping == 0 || opts->mapping == 2))
+    if (!cell && chem_coop_supported(mech->dev) && mech->dev.RPL % 2 == 0 && (opts->mapping == 0 || opts->mapping == 2))
         cands.push_back({1, 0, 4});
     // one cell per lane: 64 cells per wave, for fields where the total work, not one cell's chain
     // of sub-steps, sets the time

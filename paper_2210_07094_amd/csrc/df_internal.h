@@ -81,6 +81,13 @@ struct MechDev {
     // nu G_j eff_jl, (j, nu) packed in wdp[e]
     const int *wdo;      // [K + 1]
     const int *wdp;
+    // per-lane rows of the kernel with one wave per cell for small mechanisms (df_chem_cell.hip;
+    // field f of lane l at 64 f + l, the fields in the order its load_row reads them)
+    const double *xd;
+    const int *xi;
+    int xel;             // list entries per lane (6 or 8), 0 = the mechanism does not fit
+    int xtroe;           // falloff reactions
+    int xboth;           // 1 = some reaction has a species on both sides
 };
 
 struct HostMech {
@@ -192,6 +199,12 @@ df_status launch_chem_wave(const MechDev &m, const StepArgs &a, const int32_t *c
 bool chem_coop_supported(const MechDev &m);
 df_status launch_chem_coop(const MechDev &m, const StepArgs &a, const CellQueue &q, hipStream_t stream,
                            int halves = 1);
+// one wavefront per cell for small mechanisms (df_chem_cell.hip); q.ctr with q.order: cells claimed
+// from the order, else slot s < *dcount (or n) takes cell cidx[s] (or s); writes the tape when given
+// its queue's counters: kCellQueues of them, 128 bytes apart, zero at the launch
+constexpr int kCellQueues = 8;
+bool chem_cell_supported(const MechDev &m);
+df_status launch_chem_cell(const MechDev &m, const StepArgs &a, const CellQueue &q, hipStream_t stream);
 // persistent work-queue launch mixing the 16-lane and the one-cell-per-lane bodies
 // (df_chem_coop.hip): blocks resident at once on the current device, and the launch
 int32_t chem_queue_capacity(const MechDev &m);

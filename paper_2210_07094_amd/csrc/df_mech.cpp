@@ -450,6 +450,122 @@ static void pack_wave_tables(const HostMech &m, const CoopTables &ct, WaveTables
     if (w.dp.empty()) w.dp.push_back(pack_entry(0, 0));
 }
 
+// Per-lane rows of the one-wave-per-cell kernel for small mechanisms (fields as its load_row reads
+// them, field f of lane l at 64 f + l).  el = 0 where the mechanism does not fit: more than 32
+// reactions, a species in more reactions than four lists hold, or too few spare lanes for the
+// falloff reactions' quads (lanes beyond M in either half, aligned to four) and lane 63, whose row
+// of weights 1/W_k gives sum Y/W.
+struct CellTables {
+    std::vector<double> d;
+    std::vector<int> i;
+    int el = 0, troe = 0, both = 0;
+};
+
+static void pack_cell_tables(const HostMech &m, const CoopTables &ct, CellTables &t) {
+    const int K = m.K, M = m.M, N = K + 1, NI = (N + 3) / 4, KE = K + 4;
+    t.d.assign(1, 0.0);
+    t.i.assign(1, 0);
+    if (K < 1 || N + 2 > 16 || M < 1 || M > 31) return;
+    const int el = M <= 24 ? 6 : 8;
+    int nt = 0;
+    for (int j = 0; j < M; ++j) nt += ct.ci[size_t(j) * kCiInt] == 2;
+    std::vector<int> quads;
+    for (int h = 0; h < 64; h += 32)
+        for (int q = (M + 3) & ~3; q + 4 <= 32 && h + q + 4 < 64; q += 4) quads.push_back(h + q);
+    if (ct.lmax > 4 * el || nt > int(quads.size())) return;
+    t.el = el;
+    t.troe = nt;
+    const int nd = 7 + 6 + 2 + 5 + 3 + 3 + K + NI + 2 * el, ni = 9 + 2 + el;
+    t.d.assign(size_t(nd) * 64, 0.0);
+    t.i.assign(size_t(ni) * 64, 0);
+    // field offsets
+    const int fE = 0, fDh = 7, fIW = 13, fW = 14, fA = 15, fWq = 20, fCnt = 21, fSg = 22, fEeff = 23, fRow = 26,
+              fCol = fRow + K, fLc = fCol + NI, fNu = fLc + el;
+    const int iSl = 0, iEc = 3, iEm = 6, iSrc = 9, iFl = 10, iLi = 11;
+    auto D = [&](int f, int l) -> double & { return t.d[size_t(f) * 64 + l]; };
+    auto I = [&](int f, int l) -> int & { return t.i[size_t(f) * 64 + l]; };
+    for (int l = 0; l < 64; ++l) {
+        I(iSrc, l) = 4 * l;
+        if (l < 32) D(fDh, l) = 1.0;  // the lower half's rates are stored as they are
+        for (int e = 0; e < 3; ++e) I(iEc + e, l) = 16;  // scratch column
+        const int r = l & 15, g = l >> 4;
+        if (r >= 1 && r <= K) {
+            D(fIW, l) = 1.0 / m.W[r - 1];
+            D(fW, l) = m.W[r - 1];
+            for (int i = 0; i < 5; ++i) D(fA + i, l) = m.nasa[7 * size_t(r - 1) + i];
+        }
+        for (int i = 0; i < NI; ++i) {
+            const int c = 4 * i + g;
+            if (c >= 1 && c < N) D(fCol + i, l) = 1.0 / m.W[c - 1];
+        }
+        // list sums: row 0 adds every q_j dH_j (second half of the rate array), row 1 + k its nu q
+        for (int e = 0; e < el; ++e) {
+            const int x = 4 * e + g;
+            if (r == 0 && x < M) {
+                I(iLi + e, l) = 32 + x;
+                D(fLc + e, l) = 1.0;
+            }
+            if (r >= 1 && r <= K && x < ct.wlo[r] - ct.wlo[r - 1]) {
+                I(iLi + e, l) = ct.wlj[size_t(ct.wlo[r - 1]) + x];
+                D(fLc + e, l) = ct.wlc[size_t(ct.wlo[r - 1]) + x];
+            }
+        }
+        // stoichiometric matrix: row r, reaction 4 e + g (row 0 is filled with the enthalpies)
+        if (r >= 1 && r <= K)
+            for (int x = ct.wlo[r - 1]; x < ct.wlo[r]; ++x)
+                if (ct.wlj[x] % 4 == g) D(fNu + ct.wlj[x] / 4, l) = ct.wlc[x];
+    }
+    for (int k = 0; k < K; ++k) D(fRow + k, 63) = 1.0 / m.W[k];
+    int qn = 0;
+    for (int j = 0; j < M; ++j) {
+        const double *cr = &ct.cr[size_t(j) * kCrDbl];
+        const int *ri = &ct.ci[size_t(j) * kCiInt];
+        const int type = ri[0];
+        const int quad = type == 2 ? quads[qn++] : -1;
+        for (int side = 0; side < 2; ++side) {
+            const int l = j + 32 * side;
+            if (side == 0)
+                for (int i = 0; i < 3; ++i) D(fE + i, l) = cr[i];
+            else
+                for (int i = 0; i < 7; ++i) D(fE + i, l) = cr[3 + i];
+            if (side == 1)
+                for (int i = 0; i < 6; ++i) D(fDh + i, l) = cr[10 + i];
+            D(fCnt, l) = cr[23 + side];
+            D(fSg, l) = side == 0 ? 1.0 : -1.0;
+            for (int k = 0; k < K; ++k) D(fRow + k, l) = ct.ceffw[size_t(j) * K + k];
+            for (int s = 0; s < 3; ++s) I(iSl + s, l) = ri[1 + 3 * side + s];
+            int fl = type == 1 ? 1 : (type == 2 ? 2 : 0), e = 0;
+            for (int x = 0; x < kCoopEnt; ++x) {
+                const int sp = ri[7 + 2 * x], mk = ri[8 + 2 * x];
+                const int own = side == 0 ? (mk & 7) : (mk >> 3);
+                if (sp >= K || own == 0) continue;
+                I(iEc + e, l) = 1 + sp;
+                I(iEm + e, l) = own;
+                if (side == 1 && (mk & 7)) {
+                    fl |= 8 << e;
+                    t.both = 1;
+                }
+                D(fEeff + e, l) = ct.ceff[size_t(j) * KE + sp];
+                ++e;
+            }
+            if (quad >= 0) I(iSrc, l) = 4 * quad;
+            I(iFl, l) = fl;
+        }
+        for (int x = 0; x < 4 && quad >= 0; ++x) {
+            const int l = quad + x;
+            const double al = cr[19];
+            if (x == 0)
+                for (int i = 0; i < 3; ++i) D(fE + i, l) = cr[16 + i];
+            if (x == 1) D(fE + 3, l) = cr[20];
+            if (x == 2) D(fE + 3, l) = cr[21];
+            if (x == 3) D(fE + 2, l) = cr[22];
+            D(fWq, l) = x == 0 ? 0.0 : (x == 1 ? 1.0 - al : (x == 2 ? al : 1.0));
+            for (int k = 0; k < K; ++k) D(fRow + k, l) = ct.ceffw[size_t(j) * K + k];
+            I(iFl, l) = 4;
+        }
+    }
+}
+
 df_status validate_chem_opts(const df_chem_opts &o) {
     if (!(o.rtol > 0 && o.rtol < 1) || !(o.atol_T > 0) || !(o.atol_Y > 0) || !(o.h_min > 0) || o.max_steps < 1 ||
         o.mapping < 0 || o.mapping > 5 || o.schedule < 0 || o.schedule > 2 || o.coop_blocks < -1 ||
@@ -504,6 +620,8 @@ df_status df_mech_load(const char *path, int32_t device, df_mech **out) {
     pack_coop_tables(hm, order, ct);
     WaveTables wt;
     pack_wave_tables(hm, ct, wt);
+    CellTables xt;
+    pack_cell_tables(hm, ct, xt);
     // one allocation holding every table, each part 256-byte aligned
     struct Part {
         const void *src;
@@ -520,7 +638,8 @@ df_status df_mech_load(const char *path, int32_t device, df_mech **out) {
                     {wt.tk.data(), wt.tk.size() * 4, 0},    {wt.ell.data(), wt.ell.size() * 4, 0},
                     {wt.rb.data(), wt.rb.size() * 4, 0},    {wt.rc.data(), wt.rc.size() * 4, 0},
                     {wt.lo.data(), wt.lo.size() * 4, 0},    {wt.lp.data(), wt.lp.size() * 4, 0},
-                    {wt.dof.data(), wt.dof.size() * 4, 0},  {wt.dp.data(), wt.dp.size() * 4, 0}};
+                    {wt.dof.data(), wt.dof.size() * 4, 0},  {wt.dp.data(), wt.dp.size() * 4, 0},
+                    {xt.d.data(), xt.d.size() * 8, 0},      {xt.i.data(), xt.i.size() * 4, 0}};
     size_t total = 0;
     for (auto &q : parts) {
         q.off = total;
@@ -575,6 +694,11 @@ df_status df_mech_load(const char *path, int32_t device, df_mech **out) {
     m->dev.wlp = I(20);
     m->dev.wdo = I(21);
     m->dev.wdp = I(22);
+    m->dev.xd = D(23);
+    m->dev.xi = I(24);
+    m->dev.xel = xt.el;
+    m->dev.xtroe = xt.troe;
+    m->dev.xboth = xt.both;
     m->dev.wnr = int(wt.rb.size());
     m->dev.wsr = wt.sr;
     m->dev.wsp = wt.sp;

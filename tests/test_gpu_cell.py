@@ -1,0 +1,89 @@
+"""GPU checks of the one-wave-per-cell kernel for small mechanisms at the edges of its layout: how many
+reactions and falloff reactions fit the lanes (and the first sizes that do not, which take the 16-lane
+kernel), a species on both sides of a reaction, and the cell counts at which the queue's groups, fixed
+first units and four-cell units begin and end.
+
+Parity bar as in test_gpu_chem (<= 1e-8 relative against the oracle where the accept/reject sequences
+agree); a cell's result does not depend on who takes it, so the queue (with workspace) and the plain
+launch (without) agree bit for bit.
+"""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+from synth import fields
+from synth.mechfile import write_mech
+from synth.mechgen import generate_h2_mechanism
+from test_gpu_chem import compare
+
+pytestmark = pytest.mark.gpu
+
+
+def _with_both_sides(m):
+    """Reaction 0 becomes 2 H + H2 <=> 2 H2 (H2 on both sides)."""
+    iH, iH2 = m.index("H"), m.index("H2")
+    m.nu_reac[0], m.nu_prod[0] = 0, 0
+    m.nu_reac[0, iH], m.nu_reac[0, iH2], m.nu_prod[0, iH2] = 2, 1, 2
+    m.arrhenius[0] = (1e15, 0.0, 500.0)
+    return m
+
+
+def _step(gm, f, dt, workspace):
+    import torch
+    n = f["T"].size
+    t = {k: torch.tensor(np.ascontiguousarray(f[k]), device="cuda:0") for k in ("T", "p", "Y")}
+    st = torch.full((n,), -7, dtype=torch.int32, device="cuda:0")
+    ns = torch.full((2 * n,), -7, dtype=torch.int32, device="cuda:0")
+    rr = torch.full_like(t["Y"], -7.0)
+    gm.chem_step(t["T"], t["p"], t["Y"], dt, rr=rr, status=st, n_steps=ns,
+                 workspace=gm.workspace(n) if workspace else None)
+    torch.cuda.synchronize()
+    return {"T": t["T"].cpu().numpy(), "Y": t["Y"].cpu().numpy(), "rr": rr.cpu().numpy(), "status": st.cpu().numpy(),
+            "n_acc": ns[:n].cpu().numpy(), "n_rej": ns[n:].cpu().numpy()}
+
+
+@pytest.mark.parametrize("n_ex,n_tb,n_troe,both", [
+    (1, 1, 0, False),      # two reactions
+    (10, 3, 3, False),     # 16 reactions, three quads in the lower half
+    (18, 2, 4, False),     # 24 reactions: two quads in each half
+    (18, 4, 2, True),      # a species on both sides
+    (18, 6, 1, False),     # 25 reactions: eight list entries per lane
+    (19, 8, 1, False),     # 28 reactions: the last that leave a quad
+    (19, 11, 0, False),    # 30 reactions, no falloff
+    (19, 9, 2, False),     # 30 reactions with falloff: no lanes left, the 16-lane kernel
+])
+def test_mechanism_edges(tmp_path, n_ex, n_tb, n_troe, both):
+    import paper_2210_07094_amd as df
+    m = generate_h2_mechanism(seed=20221016, n_exchange=n_ex, n_third_body=n_tb, n_troe=n_troe)
+    if both:
+        m = _with_both_sides(m)
+    path = str(tmp_path / "m.mech")
+    write_mech(path, m)
+    gm, om = df.Mechanism(path), oracle.Mech(path)
+    f = fields.ignition_cells(m, n=65, seed=7)
+    f["T"][::5] = np.linspace(400.0, 900.0, f["T"][::5].size)
+    f["Y"] = 0.98 * f["Y"] + 0.02 * np.random.default_rng(3).dirichlet(np.ones(9), 65).T
+    print(f"case: {n_ex}+{n_tb}+{n_troe} reactions, both sides {both}", flush=True)
+    g = _step(gm, f, 1e-7, True)
+    o = om.chem_step(f["T"], f["p"], f["Y"], 1e-7, h_inout=np.zeros(65))
+    assert np.array_equal(g["status"], o["status"])
+    worst, flipped, tol_err = compare(g, o)
+    assert worst <= 1e-8, worst
+    assert flipped <= 2 and tol_err <= 10.0, (flipped, tol_err)
+
+
+@pytest.mark.parametrize("n", [1, 2, 7, 9, 63, 1023, 1024, 1025, 2047, 2049, 4095, 4097, 8191, 9001, 70001])
+def test_queue_takes_every_cell_once(h2_path, h2_mech, n):
+    import paper_2210_07094_amd as df
+    gm = df.Mechanism(h2_path)
+    f = fields.ignition_cells(h2_mech, n=n, seed=n)
+    rng = np.random.default_rng(n)
+    f["T"] = np.where(rng.random(n) < 0.7, rng.uniform(300.0, 500.0, n), f["T"])
+    f["T"][n // 2] = np.nan
+    print(f"case: {n} cells", flush=True)
+    a, b = _step(gm, f, 2e-8, True), _step(gm, f, 2e-8, False)
+    for k in a:
+        assert np.array_equal(a[k], b[k], equal_nan=True), k
+    assert a["status"][n // 2] == df.CELL_NONFINITE
+    assert np.all(np.delete(a["status"], n // 2) == df.CELL_OK)
