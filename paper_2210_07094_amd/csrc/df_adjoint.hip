@@ -1,4 +1,6 @@
-// Discrete adjoint of the detailed-chemistry step on gfx950: eight lanes per cell, FP64.
+// Discrete adjoint of the detailed-chemistry step on gfx950: the entry points, and the sweep with eight
+// lanes per cell, FP64, for the mechanisms that the one-wave-per-cell sweep (df_adjoint_cell.hip) does not
+// take.
 //
 // The step y0 = (T0, Y0) -> y(dt) is the sequence of accepted RODAS4 sub-steps of the taped
 // forward integration (df_chem_step_taped), with the step lengths held fixed: the
@@ -566,7 +568,8 @@ __global__ __launch_bounds__(256) void sum_cells_kernel(const double *__restrict
     if (t == 0) out[src[j]] = part_sum[0];
 }
 
-size_t adj_ws_bytes(int, int M, int64_t n) { return size_t(8) * size_t(M) * size_t(n); }
+// per-cell ln A adjoints, then the order of the one-wave-per-cell sweep
+size_t adj_ws_bytes(int, int M, int64_t n) { return (size_t(8) * size_t(M) + 4) * size_t(n); }
 
 size_t adj_lds_bytes(int K, int M) {
     const size_t N = size_t(K + 1), Ms = size_t(M), Ks = size_t(K);
@@ -668,10 +671,9 @@ extern "C" df_status df_chem_step_taped(const df_mech *mech, int64_t n_cells, in
     StepArgs a{n_cells, ld, dt, nullptr, p, T, Y, nullptr, nullptr, cell_status, n_steps, kernel_opts(o), DF_CELL_OK};
     a.tape = static_cast<double *>(tape);
     a.tape_cap = max_substeps;
-    const auto launch = chem_cell_supported(mech->dev) ? launch_chem_cell
-                                                       : [](const MechDev &m, const StepArgs &s, const CellQueue &q,
-                                                            hipStream_t st) { return launch_chem_coop(m, s, q, st); };
-    return launch(mech->dev, a, CellQueue{nullptr, nullptr, nullptr, nullptr, nullptr, 0},
+    if (chem_cell_supported(mech->dev))
+        return launch_taped_cell(mech->dev, a, static_cast<hipStream_t>(hip_stream));
+    return launch_chem_coop(mech->dev, a, CellQueue{nullptr, nullptr, nullptr, nullptr, nullptr, 0},
                             static_cast<hipStream_t>(hip_stream));
 }
 
@@ -720,7 +722,10 @@ extern "C" df_status df_chem_adjoint(const df_mech *mech, int64_t n_cells, int64
     const AdjArgs a{n_cells, ld,     p,      static_cast<const double *>(tape), max_substeps, T_bar, Y_bar,
                     T0_bar,  Y0_bar, lnA_bar_cells, static_cast<double *>(workspace)};
     df_status st = DF_OK;
-    switch (K) {
+    if (sweep_cell_supported(mech->dev)) {
+        st = launch_sweep_cell(mech->dev, n_cells, ld, p, a.tape, max_substeps, T_bar, Y_bar, T0_bar, Y0_bar,
+                               lnA_bar_cells, a.wth, reinterpret_cast<int32_t *>(a.wth + int64_t(M) * n_cells), s);
+    } else switch (K) {
 #define DF_CASE(k)                                   \
     case k:                                          \
         st = launch_adjoint_k<k>(mech->dev, a, s);   \

@@ -85,6 +85,10 @@ struct MechDev {
     // field f of lane l at 64 f + l, the fields in the order its load_row reads them)
     const double *xd;
     const int *xi;
+    // the reverse sweep's lists (df_adjoint_cell.hip): row lane r of species r - 1 adds up to 8 entries
+    // (index into its slot-derivative array, coefficient), field e of lane l at 64 e + l; xad null: no fit
+    const double *xad;
+    const int *xai;
     int xel;             // list entries per lane (6 or 8), 0 = the mechanism does not fit
     int xtroe;           // falloff reactions
     int xboth;           // 1 = some reaction has a species on both sides
@@ -205,6 +209,13 @@ df_status launch_chem_coop(const MechDev &m, const StepArgs &a, const CellQueue 
 constexpr int kCellQueues = 8;
 bool chem_cell_supported(const MechDev &m);
 df_status launch_chem_cell(const MechDev &m, const StepArgs &a, const CellQueue &q, hipStream_t stream);
+// the taped step on it (df_chem.hip), in cost order where that pays
+df_status launch_taped_cell(const MechDev &m, const StepArgs &a, hipStream_t stream);
+// the adjoint's reverse sweep with one wavefront per cell (df_adjoint_cell.hip)
+bool sweep_cell_supported(const MechDev &m);
+df_status launch_sweep_cell(const MechDev &m, int64_t n, int64_t ld, const double *p, const double *tape, int32_t cap,
+                            const double *Tb, const double *Yb, double *T0b, double *Y0b, double *thc, double *wth,
+                            int32_t *order, hipStream_t s);
 // persistent work-queue launch mixing the 16-lane and the one-cell-per-lane bodies
 // (df_chem_coop.hip): blocks resident at once on the current device, and the launch
 int32_t chem_queue_capacity(const MechDev &m);

@@ -459,12 +459,20 @@ struct CellTables {
     std::vector<double> d;
     std::vector<int> i;
     int el = 0, troe = 0, both = 0;
+    // slot-derivative lists of the reverse sweep: slot s of lane l at 64 s + l, d q_j/d [M] at 192 + j,
+    // T-derivative of reaction j at 224 + j; kept only where every row's list fits
+    std::vector<double> ad;
+    std::vector<int> ai;
+    bool adj = false;
 };
+constexpr int kSlotList = 8;
 
 static void pack_cell_tables(const HostMech &m, const CoopTables &ct, CellTables &t) {
     const int K = m.K, M = m.M, N = K + 1, NI = (N + 3) / 4, KE = K + 4;
     t.d.assign(1, 0.0);
     t.i.assign(1, 0);
+    t.ad.assign(1, 0.0);
+    t.ai.assign(1, 0);
     if (K < 1 || N + 2 > 16 || M < 1 || M > 31) return;
     const int el = M <= 24 ? 6 : 8;
     int nt = 0;
@@ -562,7 +570,30 @@ static void pack_cell_tables(const HostMech &m, const CoopTables &ct, CellTables
             D(fWq, l) = x == 0 ? 0.0 : (x == 1 ? 1.0 - al : (x == 2 ? al : 1.0));
             for (int k = 0; k < K; ++k) D(fRow + k, l) = ct.ceffw[size_t(j) * K + k];
             I(iFl, l) = 4;
+            I(iSrc, l) = 4 * j;
         }
+    }
+    std::vector<std::vector<std::pair<int, double>>> ent(size_t(K) + 1);
+    for (int j = 0; j < M; ++j) {
+        const int *ri = &ct.ci[size_t(j) * kCiInt];
+        ent[0].push_back({224 + j, 1.0});
+        for (int s = 0; s < 6; ++s)
+            if (ri[1 + s] > 0) ent[size_t(ri[1 + s])].push_back({64 * (s % 3) + j + (s < 3 ? 0 : 32), 1.0});
+        for (int k = 0; k < K && ri[0] != 0; ++k)
+            ent[size_t(k) + 1].push_back({192 + j, ct.ceff[size_t(j) * KE + k]});
+    }
+    t.adj = true;
+    for (auto &e : ent) t.adj = t.adj && e.size() <= size_t(4 * kSlotList);
+    if (!t.adj) return;
+    t.ad.assign(size_t(kSlotList) * 64, 0.0);
+    t.ai.assign(size_t(kSlotList) * 64, 0);
+    for (int l = 0; l < 64; ++l) {
+        const int r = l & 15, g = l >> 4;
+        for (int e = 0; e < kSlotList && r <= K; ++e)
+            if (size_t(4 * e + g) < ent[r].size()) {
+                t.ai[size_t(e) * 64 + l] = ent[r][size_t(4 * e + g)].first;
+                t.ad[size_t(e) * 64 + l] = ent[r][size_t(4 * e + g)].second;
+            }
     }
 }
 
@@ -639,7 +670,8 @@ df_status df_mech_load(const char *path, int32_t device, df_mech **out) {
                     {wt.rb.data(), wt.rb.size() * 4, 0},    {wt.rc.data(), wt.rc.size() * 4, 0},
                     {wt.lo.data(), wt.lo.size() * 4, 0},    {wt.lp.data(), wt.lp.size() * 4, 0},
                     {wt.dof.data(), wt.dof.size() * 4, 0},  {wt.dp.data(), wt.dp.size() * 4, 0},
-                    {xt.d.data(), xt.d.size() * 8, 0},      {xt.i.data(), xt.i.size() * 4, 0}};
+                    {xt.d.data(), xt.d.size() * 8, 0},      {xt.i.data(), xt.i.size() * 4, 0},
+                    {xt.ad.data(), xt.ad.size() * 8, 0},    {xt.ai.data(), xt.ai.size() * 4, 0}};
     size_t total = 0;
     for (auto &q : parts) {
         q.off = total;
@@ -696,6 +728,8 @@ df_status df_mech_load(const char *path, int32_t device, df_mech **out) {
     m->dev.wdp = I(22);
     m->dev.xd = D(23);
     m->dev.xi = I(24);
+    m->dev.xad = xt.adj ? D(25) : nullptr;
+    m->dev.xai = xt.adj ? I(26) : nullptr;
     m->dev.xel = xt.el;
     m->dev.xtroe = xt.troe;
     m->dev.xboth = xt.both;

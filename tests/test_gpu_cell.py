@@ -46,7 +46,8 @@ def _step(gm, f, dt, workspace):
 @pytest.mark.parametrize("n_ex,n_tb,n_troe,both", [
     (1, 1, 0, False),      # two reactions
     (10, 3, 3, False),     # 16 reactions, three quads in the lower half
-    (18, 2, 4, False),     # 24 reactions: two quads in each half
+    (18, 3, 3, False),     # 24 reactions: the last quad in the upper half
+    (18, 2, 4, False),     # one falloff reaction more: no lanes left, the 16-lane kernel
     (18, 4, 2, True),      # a species on both sides
     (18, 6, 1, False),     # 25 reactions: eight list entries per lane
     (19, 8, 1, False),     # 28 reactions: the last that leave a quad
@@ -87,3 +88,64 @@ def test_queue_takes_every_cell_once(h2_path, h2_mech, n):
         assert np.array_equal(a[k], b[k], equal_nan=True), k
     assert a["status"][n // 2] == df.CELL_NONFINITE
     assert np.all(np.delete(a["status"], n // 2) == df.CELL_OK)
+
+
+@pytest.mark.parametrize("n_ex,n_tb,n_troe,both", [
+    (1, 1, 0, False), (10, 3, 3, False), (18, 3, 3, False), (18, 4, 2, True), (18, 6, 0, False),
+    (18, 2, 4, False),     # no lanes left for the fourth falloff reaction: the 8-lane sweep
+])
+def test_sweep_mechanism_edges(tmp_path, n_ex, n_tb, n_troe, both):
+    """Rows of the sensitivity matrix against the oracle's, the bar of test_gpu_adjoint."""
+    import paper_2210_07094_amd as df
+    from test_gpu_adjoint import RTOL_ROW, _full_matrix, _oracle_rows, _taped
+    m = generate_h2_mechanism(seed=20221016, n_exchange=n_ex, n_third_body=n_tb, n_troe=n_troe)
+    if both:
+        m = _with_both_sides(m)
+    path = str(tmp_path / "m.mech")
+    write_mech(path, m)
+    gm, om = df.Mechanism(path), oracle.Mech(path)
+    f = fields.ignition_cells(m, n=3, seed=7)
+    f["Y"] = 0.98 * f["Y"] + 0.02 * np.random.default_rng(3).dirichlet(np.ones(9), 3).T
+    print(f"case: sweep, {n_ex}+{n_tb}+{n_troe} reactions, both sides {both}", flush=True)
+    _, p, _, tape, st, ns = _taped(gm, f, dt=2e-7, cap=4096)
+    ns = ns.cpu().numpy()
+    assert np.all(st.cpu().numpy() == df.CELL_OK)
+    G = _full_matrix(gm, p, tape, 3, cap=4096)
+    matched = 0
+    for i in range(3):
+        S, sto, nacc, nrej = _oracle_rows(m, om, f, i, dt=2e-7)
+        if (nacc, nrej) != (ns[i], ns[3 + i]):
+            continue
+        matched += 1
+        err = np.abs(G[i] - S) / np.abs(S).max(axis=1, keepdims=True)
+        assert err.max() <= RTOL_ROW, (i, err.max())
+    assert matched >= 2
+
+
+@pytest.mark.parametrize("n", [1024, 1025, 8704, 8705])
+def test_taped_step_order(h2_path, h2_mech, n):
+    """The cost order of a taped step lies in the lengths of the tape's last sub-step: a tape that is just
+    long enough gives the gradients of a longer one bit for bit, and the step is the untaped one."""
+    import torch
+    import paper_2210_07094_amd as df
+    from test_gpu_adjoint import _taped
+    gm = df.Mechanism(h2_path)
+    f = fields.ignition_cells(h2_mech, n=n, seed=3)
+    print(f"case: taped order, {n} cells", flush=True)
+    plain = _step(gm, f, 1e-7, False)
+    cap = int(plain["n_acc"].max())
+    gen = torch.Generator(device="cuda:0").manual_seed(1)
+    Tb = torch.randn(n, dtype=torch.float64, device="cuda:0", generator=gen)
+    Yb = torch.randn(9, n, dtype=torch.float64, device="cuda:0", generator=gen)
+    out = []
+    for c in (cap, cap + 7, cap - 1):
+        T, p, Y, tape, st, ns = _taped(gm, f, dt=1e-7, cap=c)
+        assert np.array_equal(T.cpu().numpy(), plain["T"]) and np.array_equal(Y.cpu().numpy(), plain["Y"])
+        full = plain["n_acc"] > c
+        assert np.array_equal(st.cpu().numpy(), np.where(full, df.CELL_TAPE_FULL, df.CELL_OK))
+        out.append([x.cpu().numpy() for x in gm.chem_adjoint(p, tape, c, Tb, Yb)[:3]])
+    ok = plain["n_acc"] <= cap - 1
+    assert ok.any() and not ok.all()
+    for a, b, c in zip(*out):
+        assert np.array_equal(a, b)
+        assert np.array_equal(a[..., ok], c[..., ok]) and np.all(c[..., ~ok] == 0)
