@@ -13,6 +13,7 @@
 #include <cstdio>
 #include <cstring>
 #include <fstream>
+#include <type_traits>
 
 #include "df_fp8.h"
 #include "df_internal.h"
@@ -48,8 +49,14 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 // Normalised network inputs and flags: 1 = network, 0 = fallback (out of training range),
 // 2 = non-finite input.  Cell i's row of in_pad bf16 inputs (zero beyond the K + 2 features, and
-// for the padding rows i >= n) is written as 16-byte pieces.  The thread of cell 0 also clears
-// the fallback counter, which the output kernel (a later launch) advances.
+// for the padding rows i >= n) is written as 16-byte pieces.  The first block also clears the fallback
+// counter, which the output kernel (a later launch) advances.
+// The time is the FP64 power of each feature (some 200 instructions), so a block of 256 threads takes 32
+// cells and spreads their features over its 8 half-waves, cells along the lanes: with one thread per
+// cell and its features in sequence, 9 species, 1 / 65,536 cells took 9.8 / 15.0 us and 53 species,
+// 65,536 cells 60 us (1,024 waves, one per SIMD); spread 4.2 / 9.5 us and 37 us.
+constexpr int kPreCells = 32;
+
 template <int K>
 __global__ __launch_bounds__(kPreThreads) void pre_kernel(DnnDevParams prm, int64_t n, int64_t n_pad, int64_t ld,
                                                           const double *__restrict__ p, const double *__restrict__ T,
@@ -58,81 +65,83 @@ __global__ __launch_bounds__(kPreThreads) void pre_kernel(DnnDevParams prm, int6
                                                           int32_t *__restrict__ count,
                                                           int32_t *__restrict__ status, double *__restrict__ rr,
                                                           int fallback) {
-    const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i >= n_pad) return;
-    if (i == 0) *count = 0;
-    u32x4 *row = reinterpret_cast<u32x4 *>(xb + i * in_pad);
-    if (i >= n) {
-        for (int c = 0; c < in_pad / 8; ++c) row[c] = u32x4{0u, 0u, 0u, 0u};
-        return;
-    }
-    constexpr int NI = K + 2;
-    double x[NI];
-    x[0] = T[i];
-    x[1] = p[i];
-    bool finite = isfinite(x[0]) && x[0] > 0.0 && isfinite(x[1]) && x[1] > 0.0;
+    constexpr int NI = K + 2, NQ = (NI + 7) / 8, LDX = 8 * NQ + 8;  // features, 16-byte pieces holding them
+    __shared__ __attribute__((aligned(16))) bf16_t xs[kPreCells * LDX];
+    __shared__ int bad[kPreCells];  // bit 0: out of range, bit 1: not finite
+    const int t = threadIdx.x, c = t % kPreCells, f0 = t / kPreCells;
+    const int64_t i0 = int64_t(blockIdx.x) * kPreCells, i = i0 + c;
+    if (blockIdx.x == 0 && t == 0) *count = 0;
+    if (t < kPreCells) bad[t] = 0;
+    for (int e = t; e < kPreCells * LDX / 8; e += kPreThreads)
+        reinterpret_cast<u32x4 *>(xs)[e] = u32x4{0u, 0u, 0u, 0u};
+    __syncthreads();
+    if (i < n) {
+        int b = 0;
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-        const double y = Y[k * ld + i];
-        finite = finite && isfinite(y);
-        x[2 + k] = boxcox(y, prm.lambda);
-    }
-    int f = 1;
-    if (!finite) {
-        f = 2;
-    } else {
-#pragma unroll
-        for (int c = 0; c < NI; ++c)
-            if (!(x[c] >= prm.lo[c] && x[c] <= prm.hi[c])) f = 0;
-    }
-    flag[i] = int8_t(f);
-    unsigned xr[(NI + 1) / 2];
-#pragma unroll
-    for (int c = 0; c < NI; c += 2) {
-        const double x0 = (x[c] - prm.mu_in[c]) / prm.sig_in[c];
-        const unsigned b0 = (f == 1) ? unsigned(f2bf(float(x0))) : 0u;
-        unsigned b1 = 0u;
-        if (c + 1 < NI) {
-            const double x1 = (x[c + 1] - prm.mu_in[c + 1]) / prm.sig_in[c + 1];
-            b1 = (f == 1) ? unsigned(f2bf(float(x1))) : 0u;
+        for (int f = f0; f < NI; f += kPreThreads / kPreCells) {
+            double x;
+            if (f < 2) {
+                x = f == 0 ? T[i] : p[i];
+                if (!(isfinite(x) && x > 0.0)) b |= 2;
+            } else {
+                const double y = Y[(f - 2) * ld + i];
+                if (!isfinite(y)) b |= 2;
+                x = boxcox(y, prm.lambda);
+            }
+            if (!(x >= prm.lo[f] && x <= prm.hi[f])) b |= 1;
+            xs[c * LDX + f] = f2bf(float((x - prm.mu_in[f]) / prm.sig_in[f]));
         }
-        xr[c / 2] = b0 | (b1 << 16);
+        if (b) atomicOr(&bad[c], b);
     }
-    constexpr int NQ = (NI + 7) / 8;  // 16-byte pieces holding features
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-        u32x4 v;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = (4 * q + e < (NI + 1) / 2) ? xr[4 * q + e] : 0u;
-        row[q] = v;
+    __syncthreads();
+    // the rows, zero where the network does not run
+    for (int e = t; e < kPreCells * (in_pad / 8); e += kPreThreads) {
+        const int r = e / (in_pad / 8), q = e % (in_pad / 8);
+        if (i0 + r >= n_pad) break;
+        u32x4 v = {0u, 0u, 0u, 0u};
+        if (q < NQ && !bad[r]) v = *reinterpret_cast<const u32x4 *>(xs + r * LDX + 8 * q);
+        *reinterpret_cast<u32x4 *>(xb + (i0 + r) * in_pad + 8 * q) = v;
     }
-    for (int q = NQ; q < in_pad / 8; ++q) row[q] = u32x4{0u, 0u, 0u, 0u};
+    if (i >= n) return;
+    const int f = (bad[c] & 2) ? 2 : (bad[c] ? 0 : 1);
+    if (f0 == 0) flag[i] = int8_t(f);
     if (f != 1 && !(f == 0 && fallback)) {
         // non-finite input, or out of range with the fallback switched off: state left as is
-        if (status) status[i] = (f == 2) ? DF_CELL_NONFINITE : DF_CELL_DNN_FALLBACK;
+        if (status && f0 == 0) status[i] = (f == 2) ? DF_CELL_NONFINITE : DF_CELL_DNN_FALLBACK;
         if (rr)
-            for (int k = 0; k < K; ++k) rr[k * ld + i] = 0.0;
+            for (int k = f0; k < K; k += kPreThreads / kPreCells) rr[k * ld + i] = 0.0;
     }
 }
 
-// output layer + stage 3.  The output layer u = W h (bf16 operands, fp32 sums) runs on the matrix
-// cores as 16 x 16 x 32 MFMAs over groups of 64 consecutive cells, with the weight rows (zero
+// output layer + stage 3, 16 cells per block of four waves.  The output layer u = W h (bf16
+// operands, fp32 sums) runs on the matrix cores as 16 x 16 x 32 MFMAs with the weight rows (zero
 // beyond the K outputs) as the first operand, so that lane l ends with outputs 4 (l / 16) + r of
-// cell l % 16 of each 16-cell tile; the products go through LDS to one lane per cell, which then
-// runs stage 3 in FP64.  The activation rows are read as 16-byte fragments, 16 rows x 64
-// contiguous bytes per load.  With at most 16 outputs (one output tile) the four waves of a block
-// share one group of 64 cells and split the reduction, wave w taking the 32-deep steps w, w + 4,
-// ...; their partial sums meet in LDS and are added in wave order, and wave 0 runs stage 3.  The
-// chain of dependent load-and-product steps of a wave is then a quarter as long, and a launch has
-// four times as many waves (65,536 cells: 4,096 instead of 1,024).  With more outputs each wave
-// takes its own 64 cells: there stage 3 holds the most registers and the longest chain.
+// cell l % 16.  The activation rows are read as 16-byte fragments, 16 rows x 64 contiguous bytes per
+// load.  With at most 16 outputs (one output tile) the four waves split the reduction, wave w
+// taking the 32-deep steps w, w + 4, ..., and their partial sums meet in LDS and are added in wave
+// order; with more outputs wave w takes output tile w.
+// Stage 3 in FP64 is what takes the time (a power per species, and a Newton iteration that needs every
+// species' enthalpy), so its species are spread over the lanes too: the powers one per thread with the
+// cells along the lanes, the sums over the species as 16 lanes per cell.  With one lane per cell it was
+// one long chain per lane: 9 species, 1 / 1,000 / 65,536 cells 13.9 / 20.4 / 35 us, 53 species, 65,536 cells
+// 172 us; spread 5.5 / 6.8 / 32 us and 147 us.
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
-constexpr int kPostThreads = 256;
-template <int K>
-constexpr int post_ksplit() { return (K + 15) / 16 == 1 ? 4 : 1; }
-template <int K>
-constexpr int post_cells_per_block() { return kPostThreads / post_ksplit<K>(); }
+constexpr int kPostThreads = 256, kPostCells = 16;
+
+// sum over the 16 lanes of a DPP row (the same bits in every lane)
+__device__ __forceinline__ double row_add(double x) {
+    auto step = [](double v, auto ctrl) {
+        const long long b = __double_as_longlong(v);
+        const unsigned l = unsigned(__builtin_amdgcn_mov_dpp(int(b), decltype(ctrl)::value, 0xf, 0xf, true));
+        const unsigned h = unsigned(__builtin_amdgcn_mov_dpp(int(b >> 32), decltype(ctrl)::value, 0xf, 0xf, true));
+        return v + __longlong_as_double((long long)((unsigned long long)h << 32 | l));
+    };
+    x = step(x, std::integral_constant<int, 0xb1>{});   // quad_perm [1, 0, 3, 2]
+    x = step(x, std::integral_constant<int, 0x4e>{});   // quad_perm [2, 3, 0, 1]
+    x = step(x, std::integral_constant<int, 0x141>{});  // row_half_mirror
+    return step(x, std::integral_constant<int, 0x140>{});  // row_mirror
+}
 
 template <int K>
 __global__ __launch_bounds__(kPostThreads) void post_kernel(DnnDevParams prm, MechDev m, int64_t n, int64_t ld,
@@ -144,125 +153,137 @@ __global__ __launch_bounds__(kPostThreads) void post_kernel(DnnDevParams prm, Me
                                                             int32_t *__restrict__ status, int renormalise,
                                                             int32_t *__restrict__ idx, int32_t *__restrict__ count,
                                                             int fallback) {
-    constexpr int NT = (K + 15) / 16;          // 16-output tiles
-    constexpr int NP = (K % 2) ? K : K + 1;    // LDS row stride in floats (odd: conflict-free reads)
-    constexpr int KS = post_ksplit<K>();       // waves sharing a group of 64 cells
-    __shared__ float su[kPostThreads / 64][64 * NP];
+    constexpr int NT = (K + 15) / 16;  // 16-output tiles
+    static_assert(NT <= 4, "an output tile per wave");
+    constexpr bool kSplit = NT == 1;
+    constexpr int NP = 16 * NT + 1;    // LDS row stride (odd: conflict-free reads)
+    constexpr int SP = NT;             // species per lane of stage 3
+    __shared__ float su[kSplit ? 4 : 1][kPostCells * NP];
+    __shared__ double s0[kPostCells * NP], s1[kPostCells * NP];
     const int lane = int(threadIdx.x) & 63, wv = int(threadIdx.x) >> 6;
     const int fr = lane & 15, fg = lane >> 4;
-    const int64_t cell0 = int64_t(blockIdx.x) * post_cells_per_block<K>() + (KS == 1 ? int64_t(wv) * 64 : 0);
-    {
-        floatx4 acc[4][NT];
-#pragma unroll
-        for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = floatx4{0.f, 0.f, 0.f, 0.f};
+    const int64_t cell0 = int64_t(blockIdx.x) * kPostCells;
+    if (kSplit || wv < NT) {
+        floatx4 acc = {0.f, 0.f, 0.f, 0.f};
         const bf16x8 zero = {};
-        for (int k0 = (KS == 1 ? 0 : 32 * wv); k0 < k_in; k0 += 32 * KS) {
-            bf16x8 wf[NT], hf[4];
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt) {
-                const int o = nt * 16 + fr;
-                wf[nt] = (o < K) ? *reinterpret_cast<const bf16x8 *>(W + int64_t(o) * k_in + k0 + fg * 8) : zero;
-            }
-#pragma unroll
-            for (int mt = 0; mt < 4; ++mt) {
-                const int64_t c = cell0 + mt * 16 + fr;
-                hf[mt] = (c < n) ? *reinterpret_cast<const bf16x8 *>(h + c * h_ld + k0 + fg * 8) : zero;
-            }
-#pragma unroll
-            for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt)
-                    acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[nt], hf[mt], acc[mt][nt], 0, 0, 0);
+        const int o = (kSplit ? 0 : wv * 16) + fr;
+        const int64_t c = cell0 + fr;
+        const bf16_t *wr = W + int64_t(o) * k_in + fg * 8, *hr = h + c * h_ld + fg * 8;
+#pragma unroll 8
+        for (int k0 = kSplit ? 32 * wv : 0; k0 < k_in; k0 += kSplit ? 128 : 32) {
+            const bf16x8 wf = (o < K) ? *reinterpret_cast<const bf16x8 *>(wr + k0) : zero;
+            const bf16x8 hf = (c < n) ? *reinterpret_cast<const bf16x8 *>(hr + k0) : zero;
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf, hf, acc, 0, 0, 0);
         }
 #pragma unroll
-        for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int o = nt * 16 + fg * 4 + r;
-                    if (o < K) su[wv][(mt * 16 + fr) * NP + o] = acc[mt][nt][r];
-                }
+        for (int r = 0; r < 4; ++r)
+            su[kSplit ? wv : 0][fr * NP + (kSplit ? 0 : wv * 16) + fg * 4 + r] = acc[r];
     }
     __syncthreads();
-    if (KS > 1 && wv > 0) return;  // wave 0 finishes the shared group
-    const int64_t i = cell0 + lane;
-    if (i >= n) return;
-    const int fl = flag[i];
-    if (fl != 1) {
-        // the fallback list for the integrator's launch (its order does not change any cell's result)
-        if (fl == 0 && fallback) idx[atomicAdd(count, 1)] = int32_t(i);
-        return;
-    }
-    float u[K];
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-        u[k] = su[wv][lane * NP + k];
-#pragma unroll
-        for (int w = 1; w < KS; ++w) u[k] += su[w][lane * NP + k];
-    }
-    // ---- stage 3, FP64
-    const double T0 = T[i], iT0 = 1.0 / T0;
+    // ---- stage 3, FP64.  One species (or NT) of one cell per thread, cells along the lanes
+    const int ca = int(threadIdx.x) % kPostCells, ka = int(threadIdx.x) / kPostCells;
+    const int64_t ia = cell0 + ca;
+    const int fa = ia < n ? int(flag[ia]) : 2;
+    // the fallback list for the integrator's launch (its order does not change any cell's result)
+    if (ka == 0 && fa == 0 && fallback) idx[atomicAdd(count, 1)] = int32_t(ia);
     // 1/lambda as an exact small integer (lambda = 0.1 gives 10): the power by squaring
     const int n_inv = (prm.inv_lambda == rint(prm.inv_lambda) && prm.inv_lambda >= 1.0 && prm.inv_lambda <= 64.0)
                           ? int(prm.inv_lambda)
                           : 0;
-    double Y0[K], Yn[K];
-    double sYW = 0.0, h0 = 0.0, sum = 0.0;
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-        Y0[k] = Y[k * ld + i];
-        const double *r = m.sp + k * kSpTab;
-        sYW += Y0[k] * r[1];
-        const double hRT = r[2] + T0 * (r[9] + T0 * (r[10] + T0 * (r[11] + T0 * r[12]))) + r[7] * iT0;
-        h0 += Y0[k] * hRT * r[1];
-        const double z1 = boxcox(Y0[k], prm.lambda) + (double(u[k] + b[k]) * prm.sig_out[k] + prm.mu_out[k]);
-        // the base clamped at 0 from below; a NaN (a non-finite network output) stays NaN, so
-        // that the cell's temperature recovery fails and it is flagged non-finite
-        const double b1 = 1.0 + prm.lambda * z1;
-        const double base = (b1 < 0.0) ? 0.0 : b1;
-        Yn[k] = n_inv ? ipow(base, n_inv) : pow(base, prm.inv_lambda);
-        sum += Yn[k];
+    for (int q = 0; q < SP; ++q) {
+        const int k = ka + 16 * q;
+        double y0 = 0.0, yn = 0.0;
+        if (k < K && fa == 1) {
+            float u = su[0][ca * NP + k];
+            if (kSplit) {
+#pragma unroll
+                for (int w = 1; w < 4; ++w) u += su[w][ca * NP + k];
+            }
+            y0 = Y[k * ld + ia];
+            const double z1 = boxcox(y0, prm.lambda) + (double(u + b[k]) * prm.sig_out[k] + prm.mu_out[k]);
+            // the base clamped at 0 from below; a NaN (a non-finite network output) stays NaN, so
+            // that the cell's temperature recovery fails and it is flagged non-finite
+            const double b1 = 1.0 + prm.lambda * z1;
+            const double base = (b1 < 0.0) ? 0.0 : b1;
+            yn = n_inv ? ipow(base, n_inv) : pow(base, prm.inv_lambda);
+        }
+        s0[ca * NP + k] = y0;
+        s1[ca * NP + k] = yn;
     }
-    h0 *= kR * T0;
+    __syncthreads();
+    // sixteen lanes per cell: the sums over the species, and T from h(T, Yn) = h0 by Newton with
+    // dh/dT = cp
+    const int cb = wv * 4 + fg;
+    const int64_t ib = cell0 + cb;
+    const bool run = ib < n && flag[ib] == 1;
+    double cf[SP][10], Yn[SP];
+    double sYW = 0.0, h0 = 0.0, sum = 0.0;
+    const double T0 = run ? T[ib] : 1.0, iT0 = 1.0 / T0;
+#pragma unroll
+    for (int q = 0; q < SP; ++q) {
+        const int k = fr + 16 * q;
+        const double *r = m.sp + (k < K ? k : 0) * kSpTab;
+        const double iW = k < K ? r[1] : 0.0;
+#pragma unroll
+        for (int e = 0; e < 5; ++e) cf[q][e] = r[2 + e] * iW;       // cp/R over 1, T .. T^4
+#pragma unroll
+        for (int e = 0; e < 4; ++e) cf[q][5 + e] = r[9 + e] * iW;   // h/(R T) over T .. T^4
+        cf[q][9] = r[7] * iW;                                       // and 1/T
+        const double y0 = s0[cb * NP + k];
+        Yn[q] = s1[cb * NP + k];
+        sYW += y0 * iW;
+        h0 += y0 * (cf[q][0] + T0 * (cf[q][5] + T0 * (cf[q][6] + T0 * (cf[q][7] + T0 * cf[q][8]))) + cf[q][9] * iT0);
+        sum += Yn[q];
+    }
+    sYW = row_add(sYW);
+    h0 = row_add(h0) * T0;
+    sum = row_add(sum);
     if (renormalise && sum > 0.0) {
         const double is = 1.0 / sum;
 #pragma unroll
-        for (int k = 0; k < K; ++k) Yn[k] *= is;
+        for (int q = 0; q < SP; ++q) Yn[q] *= is;
     }
-    // T from h(T, Yn) = h0: Newton with dh/dT = cp
     double Tn = T0;
-    bool conv = false;
-    for (int it = 0; it < 20; ++it) {
+    bool conv = false, go = run;
+    for (int it = 0; it < 20 && __ballot(go) != 0ull; ++it) {
         double hm = 0.0, cp = 0.0;
         const double iTn = 1.0 / Tn;
 #pragma unroll
-        for (int k = 0; k < K; ++k) {
-            const double *r = m.sp + k * kSpTab;
-            const double cpR = r[2] + Tn * (r[3] + Tn * (r[4] + Tn * (r[5] + Tn * r[6])));
-            const double hRT = r[2] + Tn * (r[9] + Tn * (r[10] + Tn * (r[11] + Tn * r[12]))) + r[7] * iTn;
-            hm += Yn[k] * hRT * r[1];
-            cp += Yn[k] * cpR * r[1];
+        for (int q = 0; q < SP; ++q) {
+            const double *a = cf[q];
+            cp += Yn[q] * (a[0] + Tn * (a[1] + Tn * (a[2] + Tn * (a[3] + Tn * a[4]))));
+            hm += Yn[q] * (a[0] + Tn * (a[5] + Tn * (a[6] + Tn * (a[7] + Tn * a[8]))) + a[9] * iTn);
         }
-        const double dT = (hm * Tn - h0 / kR) / cp;
-        Tn -= dT;
-        if (!isfinite(Tn)) break;
-        if (fabs(dT) <= 1e-9) {
-            conv = true;
-            break;
+        const double dT = (row_add(hm) * Tn - h0) / row_add(cp);
+        if (go) {
+            Tn -= dT;
+            conv = isfinite(Tn) && fabs(dT) <= 1e-9;
+            go = isfinite(Tn) && !conv;
         }
     }
-    if (rr) {
-        const double rdt = p[i] / (sYW * kR * T0) / dt;
+    if (run) {
+        const double rdt = rr ? p[ib] / (sYW * kR * T0) / dt : 0.0;
 #pragma unroll
-        for (int k = 0; k < K; ++k) rr[k * ld + i] = rdt * (Yn[k] - Y0[k]);
+        for (int q = 0; q < SP; ++q) {
+            const int k = fr + 16 * q;
+            s0[cb * NP + k] = rdt * (Yn[q] - s0[cb * NP + k]);
+            s1[cb * NP + k] = Yn[q];
+        }
+        if (fr == 0) {
+            T[ib] = Tn;
+            if (status) status[ib] = conv ? DF_CELL_OK : DF_CELL_NONFINITE;
+        }
     }
-    T[i] = Tn;
+    __syncthreads();
+    if (fa != 1) return;
 #pragma unroll
-    for (int k = 0; k < K; ++k) Y[k * ld + i] = Yn[k];
-    if (status) status[i] = conv ? DF_CELL_OK : DF_CELL_NONFINITE;
+    for (int q = 0; q < SP; ++q) {
+        const int k = ka + 16 * q;
+        if (k >= K) continue;
+        Y[k * ld + ia] = s1[ca * NP + k];
+        if (rr) rr[k * ld + ia] = s0[ca * NP + k];
+    }
 }
 
 int64_t round_up(int64_t a, int64_t b) { return (a + b - 1) / b * b; }
@@ -369,7 +390,7 @@ df_status launch_dnn_k(const df_dnn *d, const df_mech *m, int64_t n, int64_t ld,
     auto *idx = reinterpret_cast<int32_t *>(base + w.o_idx);
     auto *cnt = reinterpret_cast<int32_t *>(base + w.o_cnt);
     const int in_pad = d->layers[0].k_pad;
-    hipLaunchKernelGGL(pre_kernel<K>, dim3(unsigned((w.n_pad + kPreThreads - 1) / kPreThreads)), dim3(kPreThreads), 0,
+    hipLaunchKernelGGL(pre_kernel<K>, dim3(unsigned((w.n_pad + kPreCells - 1) / kPreCells)), dim3(kPreThreads), 0,
                        s, d->prm, n, w.n_pad, ld, p, T, Y, xb, in_pad, flag, cnt, status, rr, o.fallback);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(DF_E_HIP, std::string("dnn pre launch: ") + hipGetErrorString(e));
@@ -419,8 +440,7 @@ df_status launch_dnn_k(const df_dnn *d, const df_mech *m, int64_t n, int64_t ld,
         in_ld = out_ld;
     }
     const DnnLayer &Lo = d->layers.back();
-    constexpr int kCpb = post_cells_per_block<K>();
-    hipLaunchKernelGGL(post_kernel<K>, dim3(unsigned((n + kCpb - 1) / kCpb)), dim3(kPostThreads), 0, s,
+    hipLaunchKernelGGL(post_kernel<K>, dim3(unsigned((n + kPostCells - 1) / kPostCells)), dim3(kPostThreads), 0, s,
                        d->prm, m->dev, n, ld, dt, in, in_ld, Lo.W, Lo.b, Lo.k_pad, flag, p, T, Y, rr, status,
                        o.renormalise, idx, cnt, o.fallback);
     e = hipGetLastError();
