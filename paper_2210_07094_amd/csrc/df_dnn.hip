@@ -423,14 +423,14 @@ df_status launch_dnn_k(const df_dnn *d, const df_mech *m, int64_t n, int64_t ld,
             if (!a8) return fail(DF_E_UNSUPPORTED, "dnn step: FP8 needs a first layer with 32 or 64 padded inputs");
             st = launch_gemm_fp8(a8, in_ld, a8s, a8_sst, blob + bl.w8[l], L.k_pad,
                                  reinterpret_cast<const int32_t *>(blob + bl.e8[l]), L.b, out, out_ld,
-                                 q_next ? o8s : nullptr, o8_sst, w.n_pad, L.n_pad, L.k_pad, s);
+                                 q_next ? o8s : nullptr, o8_sst, w.n_pad, n, L.n_pad, L.k_pad, s);
             wrote8 = q_next;
         } else if (q_next) {
-            st = launch_gemm_bf16_fp8out(in, in_ld, L.W, L.k_pad, L.b, o8, out_ld, o8s, o8_sst, w.n_pad, L.n_pad,
-                                         L.k_pad, s);
+            st = launch_gemm_bf16_fp8out(in, in_ld, L.W, L.k_pad, L.b, o8, out_ld, o8s, o8_sst, w.n_pad, n,
+                                         L.n_pad, L.k_pad, s);
             wrote8 = true;
         } else {
-            st = launch_gemm_bf16(in, in_ld, L.W, L.k_pad, L.b, out, out_ld, w.n_pad, L.n_pad, L.k_pad, true, s);
+            st = launch_gemm_bf16(in, in_ld, L.W, L.k_pad, L.b, out, out_ld, w.n_pad, n, L.n_pad, L.k_pad, s);
         }
         if (st != DF_OK) return st;
         a8 = wrote8 ? o8 : nullptr;

@@ -254,15 +254,17 @@ struct DnnDevParams {   // kernel argument for the pre/post kernels
     const double *mu_in, *sig_in, *mu_out, *sig_out, *lo, *hi;  // device arrays
 };
 
-// C[M][N] = act(A[M][K] B[N][K]^T + bias) in bf16 with fp32 accumulation; M % kGemmBM == 0,
-// N % kGemmBN == 0, K % kGemmBK == 0, row strides in elements.
+// C[M][N] = GELU(A[M][K] B[N][K]^T + bias) in bf16 with fp32 accumulation; M % kGemmBM == 0,
+// N % kGemmBN == 0, K % kGemmBK == 0, row strides in elements.  M rows are allocated and the first `rows`
+// of them are wanted: the rows from there on may be left as they are.
 df_status launch_gemm_bf16(const bf16_t *A, int lda, const bf16_t *B, int ldb, const float *bias, bf16_t *C, int ldc,
-                           int64_t M, int N, int K, bool gelu, hipStream_t stream);
+                           int64_t M, int64_t rows, int N, int K, hipStream_t stream);
 // the same GEMM with the training epilogues: gelu_save also stores the pre-activation
 // (A B^T + bias) to P with C's layout; gelu_grad writes (A B^T) * GELU'(P) (no bias)
 enum class GemmEpi { gelu, linear, gelu_save, gelu_grad };
 df_status launch_gemm_bf16_epi(const bf16_t *A, int lda, const bf16_t *B, int ldb, const float *bias, bf16_t *C,
-                               int ldc, int64_t M, int N, int K, GemmEpi epi, bf16_t *P, hipStream_t stream);
+                               int ldc, int64_t M, int64_t rows, int N, int K, GemmEpi epi, bf16_t *P,
+                               hipStream_t stream);
 
 }  // namespace df
 

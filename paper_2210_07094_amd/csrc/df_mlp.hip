@@ -92,10 +92,11 @@ __device__ __forceinline__ float gelu_tab(float x, const float *__restrict__ tab
 
 // copies the table into the block's LDS copy in 16-byte pieces; a barrier must follow before the
 // first gelu_tab
+template <int NT = kThreads>
 __device__ __forceinline__ void copy_phi_table(float *__restrict__ lds, int t) {
     const u32x4 *src = reinterpret_cast<const u32x4 *>(kPhiTable);
     u32x4 *dst = reinterpret_cast<u32x4 *>(lds);
-    for (int i = t; i < kPhiLdsFloats / 4; i += kThreads) dst[i] = src[i];
+    for (int i = t; i < kPhiLdsFloats / 4; i += NT) dst[i] = src[i];
 }
 
 // Output staging of the inference epilogues: a wave writes rows of 160 output bytes (80 bf16 or
@@ -659,6 +660,225 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_fp8_kernel(const uint8_t *__
     }
 }
 
+// Layers of few rows.  A grid of 128 x 160 tiles is then a few blocks, each bound by the latency of its
+// serial stages (a global load, two barriers and the LDS round trip per 32 or 64 inputs), and most of
+// its rows may be padding.  Here every wave owns one small tile, 16 RT rows x 16 CT columns, over the
+// whole reduction, and loads its operand fragments straight from global memory, D 32-deep steps ahead in a
+// second set of registers: no barrier in the loop, and only the row tiles in use.  The MFMAs,
+// their operand order and the ascending K order are those of the tiled kernels, so are the epilogues, so
+// every output has the same bits.
+template <int EPI, bool Q8, int RT, int CT, int D>
+__global__ __launch_bounds__(64) void gemm_rows_kernel(const bf16_t *__restrict__ A, int lda,
+                                                            const bf16_t *__restrict__ B, int ldb,
+                                                            const float *__restrict__ bias, bf16_t *__restrict__ C,
+                                                            int ldc, uint8_t *__restrict__ S, int sst, int K,
+                                                            int n_tiles_n, bf16_t *__restrict__ P) {
+    static_assert(!Q8 || (CT == 2 && EPI == kEpiGelu), "whole 32-column blocks");
+    __shared__ __attribute__((aligned(16))) float Ptab[EPI == kEpiGelu ? kPhiLdsFloats : 4];
+    const int lane = threadIdx.x, fr = lane & 15, fg = lane >> 4;
+    const int tile_m = int(blockIdx.x) / n_tiles_n, tile_n = int(blockIdx.x) % n_tiles_n;
+    const int64_t row0 = int64_t(tile_m) * (16 * RT);
+    const int col0 = tile_n * (16 * CT);
+    const bf16_t *ap = A + (row0 + fr) * lda + fg * 8, *bp = B + int64_t(col0 + fr) * ldb + fg * 8;
+    const int steps = K / 32;
+    bf16x8 a[2][D][RT], b[2][D][CT];
+    floatx4 acc[RT][CT];
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+        for (int j = 0; j < CT; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    auto load = [&](int s0, bf16x8 (&af)[D][RT], bf16x8 (&bf)[D][CT]) {
+        if (s0 >= steps) return;
+#pragma unroll
+        for (int u = 0; u < D; ++u) {
+            const int k = 32 * min(s0 + u, steps - 1);  // past the end: the last step again, not used
+#pragma unroll
+            for (int i = 0; i < RT; ++i) af[u][i] = *reinterpret_cast<const bf16x8 *>(ap + int64_t(16 * i) * lda + k);
+#pragma unroll
+            for (int j = 0; j < CT; ++j) bf[u][j] = *reinterpret_cast<const bf16x8 *>(bp + int64_t(16 * j) * ldb + k);
+        }
+    };
+    auto mma = [&](int s0, bf16x8 (&af)[D][RT], bf16x8 (&bf)[D][CT]) {
+#pragma unroll
+        for (int u = 0; u < D; ++u) {
+            if (s0 + u >= steps) break;
+#pragma unroll
+            for (int i = 0; i < RT; ++i)
+#pragma unroll
+                for (int j = 0; j < CT; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[u][j], af[u][i], acc[i][j], 0, 0, 0);
+        }
+    };
+    load(0, a[0], b[0]);
+    if (EPI == kEpiGelu) {
+        copy_phi_table<64>(Ptab, lane);
+        __syncthreads();
+    }
+    for (int s0 = 0; s0 < steps; s0 += 2 * D) {
+        load(s0 + D, a[1], b[1]);
+        mma(s0, a[0], b[0]);
+        load(s0 + 2 * D, a[0], b[0]);
+        mma(s0 + D, a[1], b[1]);
+    }
+#pragma unroll
+    for (int i = 0; i < RT; ++i) {
+        const int64_t row = row0 + i * 16 + fr;
+        floatx4 v[CT];
+#pragma unroll
+        for (int j = 0; j < CT; ++j) {
+            const int col = col0 + j * 16 + fg * 4;
+            const int64_t off = row * ldc + col;
+            v[j] = acc[i][j] + (EPI == kEpiGeluGrad ? floatx4{0.f, 0.f, 0.f, 0.f}
+                                                    : *reinterpret_cast<const floatx4 *>(bias + col));
+            if constexpr (EPI == kEpiGeluSave) *reinterpret_cast<bf16x4 *>(P + off) = to_bf16x4(v[j]);
+            bf16x4 pv = {};
+            if constexpr (EPI == kEpiGeluGrad) pv = *reinterpret_cast<const bf16x4 *>(P + off);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                if constexpr (EPI == kEpiGelu) v[j][r] = gelu_tab(v[j][r], Ptab);
+                if constexpr (EPI == kEpiGeluSave) v[j][r] = gelu_erfc(v[j][r]);
+                if constexpr (EPI == kEpiGeluGrad) v[j][r] *= gelu_grad(float(pv[r]));
+            }
+            if constexpr (!Q8) *reinterpret_cast<bf16x4 *>(C + off) = to_bf16x4(v[j]);
+        }
+        if constexpr (Q8) {
+            uint32_t w0, w1;
+            quant_fp8_block(v[0], v[1], S, row, sst, col0, fg, w0, w1);
+            uint8_t *q = reinterpret_cast<uint8_t *>(C) + row * ldc + col0 + 4 * fg;
+            *reinterpret_cast<uint32_t *>(q) = w0;
+            *reinterpret_cast<uint32_t *>(q + 16) = w1;
+        }
+    }
+}
+
+// the same for an FP8 layer: 128-deep steps, operands and scales as in gemm_fp8_kernel
+template <bool Q8, int RT, int D>
+__global__ __launch_bounds__(64) void gemm_fp8_rows_kernel(const uint8_t *__restrict__ A8, int lda,
+                                                                const uint8_t *__restrict__ SA, int sst,
+                                                                const uint8_t *__restrict__ W8, int ldb,
+                                                                const int32_t *__restrict__ wexp,
+                                                                const float *__restrict__ bias,
+                                                                bf16_t *__restrict__ C, int ldc,
+                                                                uint8_t *__restrict__ SC, int sstc, int K,
+                                                                int n_tiles_n) {
+    constexpr int CT = 2;
+    __shared__ __attribute__((aligned(16))) float Ptab[kPhiLdsFloats];
+    const int lane = threadIdx.x, fr = lane & 15, fg = lane >> 4;
+    const int tile_m = int(blockIdx.x) / n_tiles_n, tile_n = int(blockIdx.x) % n_tiles_n;
+    const int64_t row0 = int64_t(tile_m) * (16 * RT);
+    const int col0 = tile_n * (16 * CT);
+    const uint8_t *ap = A8 + (row0 + fr) * lda, *bp = W8 + int64_t(col0 + fr) * ldb;
+    const uint8_t *sp = SA + (row0 + fr) * sst;
+    const int steps = (K + KD8 - 1) / KD8;
+    i32x8 a[2][D][RT], b[2][D][CT];
+    int sa[2][D][RT], sw[CT];
+    floatx4 acc[RT][CT];
+#pragma unroll
+    for (int j = 0; j < CT; ++j) sw[j] = 127 + wexp[col0 + j * 16 + fr];
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+        for (int j = 0; j < CT; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    // 32 bytes of a row at k0 + 16 fg and k0 + 64 + 16 fg; zeros at or beyond K
+    auto frag = [&](const uint8_t *row, int k0) {
+        const u32x4 z = {0u, 0u, 0u, 0u};
+        const int k = k0 + fg * 16;
+        const u32x4 lo = (k < K) ? *reinterpret_cast<const u32x4 *>(row + k) : z;
+        const u32x4 hi = (k + 64 < K) ? *reinterpret_cast<const u32x4 *>(row + k + 64) : z;
+        return i32x8{int(lo[0]), int(lo[1]), int(lo[2]), int(lo[3]), int(hi[0]), int(hi[1]), int(hi[2]), int(hi[3])};
+    };
+    auto load = [&](int s0, i32x8 (&af)[D][RT], int (&sf)[D][RT], i32x8 (&bf)[D][CT]) {
+#pragma unroll
+        for (int u = 0; u < D; ++u) {
+            const int k0 = KD8 * (s0 + u);
+            if (k0 >= K) break;
+#pragma unroll
+            for (int i = 0; i < RT; ++i) {
+                af[u][i] = frag(ap + int64_t(16 * i) * lda, k0);
+                const int q = k0 / kFp8Block + fg;
+                sf[u][i] = (q * kFp8Block < K) ? int(sp[int64_t(16 * i) * sst + q]) : 127;
+            }
+#pragma unroll
+            for (int j = 0; j < CT; ++j) bf[u][j] = frag(bp + int64_t(16 * j) * ldb, k0);
+        }
+    };
+    auto mma = [&](int s0, i32x8 (&af)[D][RT], int (&sf)[D][RT], i32x8 (&bf)[D][CT]) {
+#pragma unroll
+        for (int u = 0; u < D; ++u) {
+            if (s0 + u >= steps) break;
+#pragma unroll
+            for (int j = 0; j < CT; ++j)
+#pragma unroll
+                for (int i = 0; i < RT; ++i)
+                    acc[i][j] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(bf[u][j], af[u][i], acc[i][j], 0, 0, 0,
+                                                                                 sw[j], 0, sf[u][i]);
+        }
+    };
+    load(0, a[0], sa[0], b[0]);
+    copy_phi_table<64>(Ptab, lane);
+    __syncthreads();
+    for (int s0 = 0; s0 < steps; s0 += 2 * D) {
+        load(s0 + D, a[1], sa[1], b[1]);
+        mma(s0, a[0], sa[0], b[0]);
+        load(s0 + 2 * D, a[0], sa[0], b[0]);
+        mma(s0 + D, a[1], sa[1], b[1]);
+    }
+#pragma unroll
+    for (int i = 0; i < RT; ++i) {
+        const int64_t row = row0 + i * 16 + fr;
+        floatx4 v[CT];
+#pragma unroll
+        for (int j = 0; j < CT; ++j) {
+            const int col = col0 + j * 16 + fg * 4;
+            v[j] = acc[i][j] + *reinterpret_cast<const floatx4 *>(bias + col);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[j][r] = gelu_tab(v[j][r], Ptab);
+            if constexpr (!Q8) *reinterpret_cast<bf16x4 *>(C + row * ldc + col) = to_bf16x4(v[j]);
+        }
+        if constexpr (Q8) {
+            uint32_t w0, w1;
+            quant_fp8_block(v[0], v[1], SC, row, sstc, col0, fg, w0, w1);
+            uint8_t *q = reinterpret_cast<uint8_t *>(C) + row * ldc + col0 + 4 * fg;
+            *reinterpret_cast<uint32_t *>(q) = w0;
+            *reinterpret_cast<uint32_t *>(q + 16) = w1;
+        }
+    }
+}
+
+// Rows and columns, in 16s, of a wave's tile for `rows` rows of an N x K layer; 0 = the tiled kernels.  A
+// wave's tile re-reads its operands (no sharing between waves), so the rows kernel's time grows with waves x K
+// once the CUs are full, while a tiled launch of less than a wave of blocks takes the same time
+// for any row count.  Measured, rows kernel / tiled kernel in us, N x K, rows:
+//   16-wide tile, 800 x 1600: 1 row 6.9 / 27, 128 rows 10.2 / 27; 400 x 800: 128 rows 4.3 / 19
+//   32-wide, 800 x 1600: 512 rows (400 waves) 16.5 / 27.5, 1,000 (800) 26.8 / 27.6, 2,048 (1,600) 44 / 28
+//   32-wide, 400 x 800:  2,048 rows (832) 12.3 / 22.9, 4,096 (1,664) 21.0 / 23.2, 8,192 38 / 24
+//   32-wide, 1600 x 800 (backward): 1,024 rows (1,600) 18.2 / 25.9, 2,048 (3,200) 33 / 26
+//   32-wide, 1600 x 32:  512 rows (800) 5.8 / 7.6, 1,000 (1,600) 7.7 / 7.7, 2,048 11.5 / 9.0
+//   32-wide, FP8, 800 x 1600: 1 row 9.9 / 27, 1,000 rows 15.3 / 26.4, 2,048 (1,600) 21.6 / 26.7, 4,096 39 / 29
+//   32-wide, FP8, 1600 x 3200: 1,000 rows (1,600) 48.5 / 46.3
+int rows_tile(int64_t rows, int N, int K, bool fp8_in, bool fp8_out) {
+    if (!fp8_in && !fp8_out && (rows + 15) / 16 * (N / 16) <= 800) return 1;
+    const int64_t waves = (rows + 31) / 32 * (N / 32);
+    return (waves <= 1600 && waves * K <= (fp8_in ? 2700000 : 1300000)) ? 2 : 0;
+}
+
+// Q8: only the 32-wide tile; training epilogues too (their row counts are whole multiples of 128)
+template <int EPI, bool Q8>
+void launch_rows(int tile, const bf16_t *A, int lda, const bf16_t *B, int ldb, const float *bias, bf16_t *C, int ldc,
+                 uint8_t *S, int sst, int64_t rows, int N, int K, bf16_t *P, hipStream_t stream) {
+    if constexpr (EPI == kEpiGelu && !Q8) {
+        if (tile == 1) {
+            const int tn = N / 16;
+            hipLaunchKernelGGL((gemm_rows_kernel<EPI, false, 1, 1, 13>), dim3(unsigned((rows + 15) / 16 * tn)), dim3(64),
+                               0, stream, A, lda, B, ldb, bias, C, ldc, S, sst, K, tn, P);
+            return;
+        }
+    }
+    const int tn = N / 32;
+    hipLaunchKernelGGL((gemm_rows_kernel<EPI, Q8, 2, 2, 5>), dim3(unsigned((rows + 31) / 32 * tn)),
+                       dim3(64), 0, stream, A, lda, B, ldb, bias, C, ldc, S, sst, K, tn, P);
+}
+
 // the shallow-reduction layer (K = 32 or 64, shapes checked by the caller): about two blocks per
 // CU, each on one 160-column panel and every G-th row tile; S != nullptr: FP8 output (C holds the
 // E4M3FN bytes with row stride ldc, S the block scales with row stride sst)
@@ -695,14 +915,14 @@ df_status launch_shallow(const bf16_t *A, int lda, const bf16_t *B, int ldb, con
 }  // namespace
 
 df_status launch_gemm_bf16(const bf16_t *A, int lda, const bf16_t *B, int ldb, const float *bias, bf16_t *C, int ldc,
-                           int64_t M, int N, int K, bool gelu, hipStream_t stream) {
-    return launch_gemm_bf16_epi(A, lda, B, ldb, bias, C, ldc, M, N, K, gelu ? GemmEpi::gelu : GemmEpi::linear, nullptr,
-                                stream);
+                           int64_t M, int64_t rows, int N, int K, hipStream_t stream) {
+    return launch_gemm_bf16_epi(A, lda, B, ldb, bias, C, ldc, M, rows, N, K, GemmEpi::gelu, nullptr, stream);
 }
 
 df_status launch_gemm_bf16_epi(const bf16_t *A, int lda, const bf16_t *B, int ldb, const float *bias, bf16_t *C,
-                               int ldc, int64_t M, int N, int K, GemmEpi epi, bf16_t *P, hipStream_t stream) {
-    if (M % BM || N % BN || K % BK || K <= 0 || lda % 8 || ldb % 8)
+                               int ldc, int64_t M, int64_t rows, int N, int K, GemmEpi epi, bf16_t *P,
+                               hipStream_t stream) {
+    if (rows < 0 || rows > M || M % BM || N % BN || K % BK || K <= 0 || lda % 8 || ldb % 8)
         return fail(DF_E_INVALID, "gemm: shapes must be multiples of the tile sizes");
     // the outputs of every epilogue but the linear one are written as 16-byte row pieces
     if (epi != GemmEpi::linear && ((reinterpret_cast<uintptr_t>(C) & 15) || ldc % 8 ||
@@ -713,6 +933,18 @@ df_status launch_gemm_bf16_epi(const bf16_t *A, int lda, const bf16_t *B, int ld
     if (M == 0) return DF_OK;
     const int64_t tiles = (M / BM) * (N / BN);
     if (tiles > 0x7fffffff) return fail(DF_E_UNSUPPORTED, "gemm: too many tiles");
+    if (const int tile = epi == GemmEpi::linear ? 0 : rows_tile(rows, N, K, false, false)) {
+        if (rows == 0) return DF_OK;
+        if (epi == GemmEpi::gelu)
+            launch_rows<kEpiGelu, false>(tile, A, lda, B, ldb, bias, C, ldc, nullptr, 0, rows, N, K, nullptr, stream);
+        else if (epi == GemmEpi::gelu_save)
+            launch_rows<kEpiGeluSave, false>(tile, A, lda, B, ldb, bias, C, ldc, nullptr, 0, rows, N, K, P, stream);
+        else
+            launch_rows<kEpiGeluGrad, false>(tile, A, lda, B, ldb, bias, C, ldc, nullptr, 0, rows, N, K, P, stream);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return fail(DF_E_HIP, std::string("gemm launch: ") + hipGetErrorString(e));
+        return DF_OK;
+    }
     if (epi == GemmEpi::gelu && (K == 32 || K == 64))
         return launch_shallow(A, lda, B, ldb, bias, C, ldc, nullptr, 0, M, N, K, stream);
     const dim3 g = dim3(unsigned(tiles)), b = dim3(kThreads);
@@ -743,18 +975,26 @@ df_status launch_gemm_bf16_epi(const bf16_t *A, int lda, const bf16_t *B, int ld
 }
 
 df_status launch_gemm_bf16_fp8out(const bf16_t *A, int lda, const bf16_t *B, int ldb, const float *bias, uint8_t *Q,
-                                  int ldq, uint8_t *S, int sst, int64_t M, int N, int K, hipStream_t stream) {
-    if (M % BM || N % BN || lda % 8 || ldb % 8 || ldq % 16 || sst % 16 || sst < N / kFp8Block || !Q || !S)
+                                  int ldq, uint8_t *S, int sst, int64_t M, int64_t rows, int N, int K,
+                                  hipStream_t stream) {
+    if (rows < 0 || rows > M || M % BM || N % BN || lda % 8 || ldb % 8 || ldq % 16 || sst % 16 || sst < N / kFp8Block || !Q || !S)
         return fail(DF_E_INVALID, "gemm: shapes must be multiples of the tile sizes");
     if (K != 32 && K != 64) return fail(DF_E_UNSUPPORTED, "gemm with FP8 output: only a reduction depth of 32 or 64");
     if (M == 0) return DF_OK;
+    if (rows > 0 && rows_tile(rows, N, K, false, true)) {
+        launch_rows<kEpiGelu, true>(2, A, lda, B, ldb, bias, reinterpret_cast<bf16_t *>(Q), ldq, S, sst, rows, N, K, nullptr,
+                                    stream);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return fail(DF_E_HIP, std::string("gemm launch: ") + hipGetErrorString(e));
+        return DF_OK;
+    }
     return launch_shallow(A, lda, B, ldb, bias, reinterpret_cast<bf16_t *>(Q), ldq, S, sst, M, N, K, stream);
 }
 
 df_status launch_gemm_fp8(const uint8_t *A8, int lda, const uint8_t *S, int sst, const uint8_t *W8, int ldb,
                           const int32_t *wexp, const float *bias, bf16_t *C, int ldc, uint8_t *SC, int sstc,
-                          int64_t M, int N, int K, hipStream_t stream) {
-    if (M % BM || N % BN || K % kFp8Block || K <= 0 || lda % 16 || ldb % 16 || sst % 16 || lda < K || ldb < K ||
+                          int64_t M, int64_t rows, int N, int K, hipStream_t stream) {
+    if (rows < 0 || rows > M || M % BM || N % BN || K % kFp8Block || K <= 0 || lda % 16 || ldb % 16 || sst % 16 || lda < K || ldb < K ||
         sst < K / kFp8Block || (SC && (ldc % 16 || sstc % 16 || sstc < N / kFp8Block)))
         return fail(DF_E_INVALID, "gemm fp8: shapes must be multiples of the tile sizes (rows of 16 bytes)");
     if (!A8 || !S || !W8 || !wexp) return fail(DF_E_INVALID, "gemm fp8: null activation, scale, weight or exponent array");
@@ -764,7 +1004,16 @@ df_status launch_gemm_fp8(const uint8_t *A8, int lda, const uint8_t *S, int sst,
     if (M == 0) return DF_OK;
     const int64_t tiles = (M / BM) * (N / BN);
     if (tiles > 0x7fffffff) return fail(DF_E_UNSUPPORTED, "gemm fp8: too many tiles");
-    if (SC)
+    if (rows > 0 && rows_tile(rows, N, K, true, SC != nullptr)) {
+        const int tn = N / 32;
+        const dim3 g = dim3(unsigned((rows + 31) / 32 * tn)), b = dim3(64);
+        if (SC)
+            hipLaunchKernelGGL((gemm_fp8_rows_kernel<true, 2, 2>), g, b, 0, stream, A8, lda, S, sst, W8, ldb, wexp,
+                               bias, C, ldc, SC, sstc, K, tn);
+        else
+            hipLaunchKernelGGL((gemm_fp8_rows_kernel<false, 2, 2>), g, b, 0, stream, A8, lda, S, sst, W8, ldb,
+                               wexp, bias, C, ldc, SC, sstc, K, tn);
+    } else if (SC)
         hipLaunchKernelGGL(gemm_fp8_kernel<true>, dim3(unsigned(tiles)), dim3(kThreads), 0, stream, A8, lda, S, sst, W8,
                            ldb, wexp, bias, C, ldc, SC, sstc, K, N / BN);
     else

@@ -684,7 +684,7 @@ df_status df_dnn_train_step(df_trainer *t, int64_t batch, const float *x, const 
     int in_ld = L0.k_pad;
     for (int l = 0; l < nh && st == DF_OK; ++l) {
         const DnnLayer &Ly = d->layers[l];
-        st = launch_gemm_bf16_epi(in, in_ld, Ly.W, Ly.k_pad, Ly.b, t->h[l], Ly.n_pad, Bp, Ly.n_pad, Ly.k_pad,
+        st = launch_gemm_bf16_epi(in, in_ld, Ly.W, Ly.k_pad, Ly.b, t->h[l], Ly.n_pad, Bp, Bp, Ly.n_pad, Ly.k_pad,
                                   GemmEpi::gelu_save, t->a[l], s);
         in = t->h[l];
         in_ld = Ly.n_pad;
@@ -723,7 +723,7 @@ df_status df_dnn_train_step(df_trainer *t, int64_t batch, const float *x, const 
             chk("weight gradient sum");
         }
         if (l > 0 && st == DF_OK)
-            st = launch_gemm_bf16_epi(t->da[l], Ly.n_pad, t->WT[l], Ly.n_pad, nullptr, t->da[l - 1], Ly.k_pad, Bp,
+            st = launch_gemm_bf16_epi(t->da[l], Ly.n_pad, t->WT[l], Ly.n_pad, nullptr, t->da[l - 1], Ly.k_pad, Bp, Bp,
                                       Ly.k_pad, Ly.n_pad, GemmEpi::gelu_grad, t->a[l - 1], s);
     }
     if (st == DF_OK && loss) {

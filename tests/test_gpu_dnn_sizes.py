@@ -4,9 +4,10 @@ the call.
 Every sum of the step (the layers' reductions, the sums over the species) runs in an order that the
 row count does not change, so the first n cells of a large call and a call of these n cells give the
 same bits; the large call itself is held to the oracle by the parity tests.  The counts sit at the
-edges of the 16-cell output tiles, the 32-cell input tiles and the 128-row layer tiles.  Cells
-outside the training range and with non-finite input are mixed in, and the field's leading dimension
-exceeds n: those cells and the columns beyond n stay as they were.
+edges of the 16-cell output tiles, the 32-cell input tiles and the 128-row layer tiles, and of the
+row counts at which the layers of these networks change their tile.  Cells outside the training
+range and with non-finite input are mixed in, and the field's leading dimension exceeds n: those
+cells and the columns beyond n stay as they were.
 """
 import numpy as np
 import pytest
@@ -17,7 +18,7 @@ from test_gpu_dnn_large import HC_MECH
 
 pytestmark = pytest.mark.gpu
 
-SIZES = [1, 15, 16, 17, 31, 33, 127, 129, 1009]
+SIZES = [1, 15, 16, 17, 31, 33, 127, 129, 257, 1009, 1025, 2081, 4200]
 LARGE = 12000
 
 
