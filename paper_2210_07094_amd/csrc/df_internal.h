@@ -261,7 +261,7 @@ df_status launch_gemm_bf16(const bf16_t *A, int lda, const bf16_t *B, int ldb, c
                            int64_t M, int64_t rows, int N, int K, hipStream_t stream);
 // the same GEMM with the training epilogues: gelu_save also stores the pre-activation
 // (A B^T + bias) to P with C's layout; gelu_grad writes (A B^T) * GELU'(P) (no bias)
-enum class GemmEpi { gelu, linear, gelu_save, gelu_grad };
+enum class GemmEpi { gelu, gelu_save, gelu_grad };
 df_status launch_gemm_bf16_epi(const bf16_t *A, int lda, const bf16_t *B, int ldb, const float *bias, bf16_t *C,
                                int ldc, int64_t M, int64_t rows, int N, int K, GemmEpi epi, bf16_t *P,
                                hipStream_t stream);

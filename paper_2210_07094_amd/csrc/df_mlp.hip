@@ -5,16 +5,17 @@
 // with v_mfma_f32_16x16x32_bf16, GELU epilogue, bf16 output.
 // Block tile 128 x 160 with four wave64s in a 2 x 2 arrangement, each wave
 // owning a 64 x 80 sub-tile (4 x 5 MFMA tiles); operands are staged through
-// LDS 32 or 64 deep in K (64 where K allows it) with the next stage's global
-// loads issued before the current stage's MFMAs.  The MFMAs take the weight
+// LDS 64 deep in K by loads that write LDS directly, one or three stages ahead
+// of the MFMAs.  The MFMAs take the weight
 // fragment as their first operand, so that each lane ends with four consecutive
 // outputs of one row, converted with one packed bf16 conversion pair: the GELU
 // epilogues (inference, with GELU from an LDS table, and the training forward and
-// backward) stage them per wave in LDS and write 16-byte row pieces; the linear
-// epilogue writes them with one 8-byte store.  Tiles sharing the same rows of A are mapped to the same XCD so the A
+// backward) stage them per wave in LDS and write 16-byte row pieces.  Tiles sharing
+// the same rows of A are mapped to the same XCD so the A
 // panel is fetched into that XCD's L2 once.
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "df_fp8.h"
 #include "df_internal.h"
@@ -132,20 +133,103 @@ __device__ __forceinline__ void stage_flush(const uint8_t *stg, uint8_t *dst, in
 
 // Epilogues: inference (bias, GELU); training forward (bias, GELU, and the pre-activation
 // stored to P with C's layout); training backward (the product times GELU'(P), no bias).
-enum { kEpiGelu = 0, kEpiLinear = 1, kEpiGeluSave = 2, kEpiGeluGrad = 3 };
+enum { kEpiGelu = 0, kEpiGeluSave = 2, kEpiGeluGrad = 3 };
 
-// KD: reduction depth staged per barrier pair (32, or 64 where K allows it)
-// (the 32-deep kernel at three blocks per CU: at most 168 registers, measured 4-6 % faster on
-// the 800 -> 400 layer; the 64-deep one keeps two, where the register cap cost 15 %)
-template <int EPI, int KD>
-__global__ __launch_bounds__(kThreads, KD == 32 ? 3 : 1) void gemm_kernel(const bf16_t *__restrict__ A, int lda,
+// Operand stages in LDS: 128 bytes of the reduction per row (64 bf16 or 128 FP8 values), the rows of
+// A, then the BN rows of B.  A stage is filled by loads that write LDS directly (16 bytes a
+// lane: lane l of an instruction writes the 16 bytes at base + 16 l), so no register holds it and several
+// stages are in flight.  The rows are unpadded for that; instead chunk c of row r lies at chunk
+// c ^ (r % 8), which the loading lane arranges by its global address, so that the 8 lanes of a
+// fragment read that take the same chunk of 8 rows touch all the banks.
+constexpr int kStRowB = 128, kABytes = BM * kStRowB, kStageB = kABytes + BN * kStRowB;
+
+typedef __attribute__((address_space(3))) void lds_void;
+
+// buffer descriptor of `bytes` bytes from p (the same in every lane): the loads then need one 32-bit lane offset,
+// and the rest of the address stays in scalar registers
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void *p, int bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, bytes, 0x00027000);
+}
+
+// 8 NI rows of a stage, 8 rows per instruction: this lane's 16 bytes of the first instruction lie at off + base,
+// `step` is the bytes of 8 rows
+template <int NI>
+__device__ __forceinline__ void dma_rows(__amdgpu_buffer_rsrc_t src, int off, int base, int step, uint8_t *dst) {
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(src, (lds_void *)(dst + i * 1024), 16, off, base + i * step, 0, 0);
+}
+
+// All but the last N vector loads of this wave have landed, then the same for the block (and every wave has read
+// its last fragments of the stage before).  Only the stage loads are issued in a stage loop, so N
+// counts whole stages.
+template <int N>
+__device__ __forceinline__ void stage_barrier() {
+    asm volatile("" ::: "memory");
+    // vmcnt(N) lgkmcnt(0), known to the compiler's own wait counting
+    __builtin_amdgcn_s_waitcnt((N & 15) | (N >> 4) << 14 | 0x0070);
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
+// The stage loop (NST = 2 or 4, or 1 for a single stage): NST - 1 stages are loaded ahead; a stage's buffer is refilled after the barrier that follows
+// its last read.  Separate arrays, a loop unrolled over them and loads without a branch let the
+// compiler see that a read of one stage does not wait for the loads of another: a load
+// beyond the last stage, or of a lane beyond K, is out of the descriptor's range and reads no memory (what
+// it leaves in LDS is not read).
+constexpr int kNoRow = 0x7ff00000;  // lane offset beyond every descriptor's range
+
+template <int NST, int L, class Load, class Mma>
+__device__ __forceinline__ void stage_loop(int S, uint8_t *b0, uint8_t *b1, uint8_t *b2, uint8_t *b3, Load load, Mma mma) {
+    load(0, b0);
+    if constexpr (NST == 1) {
+        stage_barrier<0>();
+        mma(0, b0);
+        stage_barrier<0>();
+        return;
+    }
+    if constexpr (NST > 2) {
+        load(1, b1);
+        load(2, b2);
+    }
+    auto step = [&](int s, uint8_t *cur, uint8_t *nxt) {
+        stage_barrier<(NST > 2 ? NST - 2 : 0) * L>();
+        load(s + NST - 1, nxt);
+        mma(s, cur);
+    };
+    int s = 0;
+    for (; s + NST <= S; s += NST) {
+        step(s, b0, NST > 2 ? b3 : b1);
+        step(s + 1, b1, b0);
+        if constexpr (NST > 2) {
+            step(s + 2, b2, b1);
+            step(s + 3, b3, b2);
+        }
+    }
+    if (s < S) step(s, b0, NST > 2 ? b3 : b1);
+    if (NST > 2 && s + 1 < S) step(s + 1, b1, b0);
+    if (NST > 2 && s + 2 < S) step(s + 2, b2, b1);
+    stage_barrier<0>();  // every load has landed and every wave has read its last fragments
+}
+
+// What bounds it: with one block per CU a 64-deep stage takes about 0.9 us however the loads are hidden (18
+// fragment reads and 40 MFMAs of 16 cycles per wave between barriers); two blocks overlap.  Staged through registers, with padded rows and two
+// barriers per stage, 65,536 rows took 216 us (1600 -> 800) and 87 us (800 -> 400); with direct LDS loads and
+// one barrier 188 us (890 TFLOP/s) and 79 us.  256-row tiles (waves of 128 x 80, one block per CU, three
+// stages) took 275 us: one wave per SIMD hides too little, and the accumulators moved between register files.
+// NST: stages in LDS (1 for K <= 64).
+template <int EPI, int NST>
+__global__ __launch_bounds__(kThreads, NST == 4 ? 1 : NST == 2 ? 2 : 3) void gemm_kernel(const bf16_t *__restrict__ A, int lda,
                                                        const bf16_t *__restrict__ B, int ldb,
                                                        const float *__restrict__ bias, bf16_t *__restrict__ C,
-                                                       int ldc, int K, int n_tiles_n, bf16_t *__restrict__ P) {
-    constexpr int LDKD = KD + 16;  // LDS row stride in bf16 (96 bytes at KD = 32)
-    // the operand stages; after the stage loop the inference epilogue stages its outputs here
-    __shared__ __attribute__((aligned(16))) bf16_t ABs[(BM + BN) * LDKD];
-    bf16_t *const As = ABs, *const Bs = ABs + BM * LDKD;
+                                                       int ldc, int K, int n_tiles_n,
+                                                       bf16_t *__restrict__ P) {
+    constexpr int kNa = BM / 32, kNb = BN / 32;  // load instructions of a wave per stage (8 rows each)
+    // the operand stages; after the stage loop the epilogues stage their outputs in the first
+    __shared__ __attribute__((aligned(1024))) uint8_t St0[kStageB];
+    __shared__ __attribute__((aligned(1024))) uint8_t St1[NST > 1 ? kStageB : 16];
+    __shared__ __attribute__((aligned(1024))) uint8_t St2[NST > 2 ? kStageB : 16];
+    __shared__ __attribute__((aligned(1024))) uint8_t St3[NST > 2 ? kStageB : 16];
     __shared__ __attribute__((aligned(16))) float Ptab[EPI == kEpiGelu ? kPhiLdsFloats : 4];
 
     // XCD-aware tile order: workgroups are dispatched round-robin over the 8 XCDs, so
@@ -159,40 +243,18 @@ __global__ __launch_bounds__(kThreads, KD == 32 ? 3 : 1) void gemm_kernel(const 
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
     const int wm = w >> 1, wn = w & 1;
 
-    // global -> register staging: A has BM*KD/8 16-byte chunks (512 at KD = 32), B has BN*KD/8 (640)
-    constexpr int kAChunks = BM * KD / 8, kBChunks = BN * KD / 8;
-    constexpr int kAPer = kAChunks / kThreads;
-    constexpr int kBPer = (kBChunks + kThreads - 1) / kThreads;
-    u32x4 ra[kAPer], rb[kBPer];
-    auto load = [&](int k0) {
-#pragma unroll
-        for (int i = 0; i < kAPer; ++i) {
-            const int c = t + i * kThreads, r = c / (KD / 8), kc = c % (KD / 8);
-            ra[i] = *reinterpret_cast<const u32x4 *>(A + (row0 + r) * lda + k0 + kc * 8);
-        }
-#pragma unroll
-        for (int i = 0; i < kBPer; ++i) {
-            const int c = t + i * kThreads;
-            if (c < kBChunks) {
-                const int r = c / (KD / 8), kc = c % (KD / 8);
-                rb[i] = *reinterpret_cast<const u32x4 *>(B + int64_t(col0 + r) * ldb + k0 + kc * 8);
-            }
-        }
-    };
-    auto store = [&]() {
-#pragma unroll
-        for (int i = 0; i < kAPer; ++i) {
-            const int c = t + i * kThreads, r = c / (KD / 8), kc = c % (KD / 8);
-            *reinterpret_cast<u32x4 *>(As + r * LDKD + kc * 8) = ra[i];
-        }
-#pragma unroll
-        for (int i = 0; i < kBPer; ++i) {
-            const int c = t + i * kThreads;
-            if (c < kBChunks) {
-                const int r = c / (KD / 8), kc = c % (KD / 8);
-                *reinterpret_cast<u32x4 *>(Bs + r * LDKD + kc * 8) = rb[i];
-            }
-        }
+    // wave w fills rows 32 w .. of A and 40 w .. of B (8 rows per instruction)
+    const int lr = lane >> 3, lc = (lane & 7) ^ lr;  // row of 8, and the chunk that belongs at chunk lane % 8
+    const int wu = __builtin_amdgcn_readfirstlane(w);
+    const int ra = 8 * kNa * wu, rb = 8 * kNb * wu;
+    const int sta = 16 * lda, stb = 16 * ldb;  // bytes of 8 rows
+    const __amdgpu_buffer_rsrc_t ba = buffer_of(A + (row0 + ra) * lda, kNa * sta),
+                                 bb = buffer_of(B + int64_t(col0 + rb) * ldb, kNb * stb);
+    const int oa = lr * 2 * lda + lc * 16, ob = lr * 2 * ldb + lc * 16;
+    auto load = [&](int s, uint8_t *st) {
+        const bool in = lc * 8 < K - 64 * s;  // the last stage may hold 32 inputs: its other chunks are not read
+        dma_rows<kNa>(ba, in ? oa : kNoRow, 128 * s, sta, st + ra * kStRowB);
+        dma_rows<kNb>(bb, in ? ob : kNoRow, 128 * s, stb, st + kABytes + rb * kStRowB);
     };
 
     floatx4 acc[TM][TN];
@@ -202,101 +264,84 @@ __global__ __launch_bounds__(kThreads, KD == 32 ? 3 : 1) void gemm_kernel(const 
         for (int j = 0; j < TN; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
 
     // MFMA 16x16x32 operands: lane l supplies row (l % 16) of the A tile and column (l % 16) of
-    // the B tile, with 8 consecutive k values starting at 8 * (l / 16)
-    const int fr = lane & 15, fk = (lane >> 4) * 8;
-    load(0);
-    if (EPI == kEpiGelu) copy_phi_table(Ptab, t);  // visible after the stage loop's first barrier
-    for (int k0 = 0; k0 < K; k0 += KD) {
-        __syncthreads();
-        store();
-        __syncthreads();
-        if (k0 + KD < K) load(k0 + KD);
-        // the staged depth in 32-deep MFMA steps, in k order (the sums are those of KD = 32)
+    // the B tile, with 8 consecutive k values (one chunk) starting at 8 * (l / 16)
+    const int fr = lane & 15, fg = lane >> 4;
+    const int fa = (wm * WM + fr) * kStRowB, fb = kABytes + (wn * WN + fr) * kStRowB;
+    // one stage in STEPS 32-deep MFMA steps, in k order
+    auto mma = [&](const uint8_t *st, auto STEPS) {
 #pragma unroll
-        for (int kk = 0; kk < KD; kk += 32) {
+        for (int kk = 0; kk < decltype(STEPS)::value; ++kk) {
+            const int c = ((4 * kk + fg) ^ (fr & 7)) * 16;
             bf16x8 af[TM], bfr[TN];
 #pragma unroll
-            for (int i = 0; i < TM; ++i)
-                af[i] = *reinterpret_cast<const bf16x8 *>(As + (wm * WM + i * 16 + fr) * LDKD + kk + fk);
+            for (int i = 0; i < TM; ++i) af[i] = *reinterpret_cast<const bf16x8 *>(st + fa + i * 16 * kStRowB + c);
 #pragma unroll
-            for (int j = 0; j < TN; ++j)
-                bfr[j] = *reinterpret_cast<const bf16x8 *>(Bs + (wn * WN + j * 16 + fr) * LDKD + kk + fk);
+            for (int j = 0; j < TN; ++j) bfr[j] = *reinterpret_cast<const bf16x8 *>(st + fb + j * 16 * kStRowB + c);
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
                 for (int j = 0; j < TN; ++j)
                     acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[j], af[i], acc[i][j], 0, 0, 0);
         }
-    }
-
+    };
+    if (EPI == kEpiGelu) copy_phi_table(Ptab, t);  // visible after the stage loop's barriers
+    stage_loop<NST, kNa + kNb>((K + 63) / 64, St0, St1, St2, St3, load, [&](int s, const uint8_t *st) {
+        if (K - 64 * s >= 64)
+            mma(st, std::integral_constant<int, 2>{});
+        else
+            mma(st, std::integral_constant<int, 1>{});
+    });
     // epilogue: with the weights as the first MFMA operand, lane l holds row (l % 16) and the four
     // columns 4 * (l / 16) + r of each 16 x 16 tile
-    if constexpr (EPI != kEpiLinear) {
-        // staged through the operand buffers, in two halves of 32 rows per wave; the training
-        // forward stages its pre-activations (P) first and then its outputs
-        static_assert(4 * 32 * kStgStrideB <= (BM + BN) * LDKD * 2 && WN * 2 == kStgRowB, "staging");
-        __syncthreads();  // every wave has read its last operand fragments
-        uint8_t *const stg = reinterpret_cast<uint8_t *>(ABs) + w * (32 * kStgStrideB);
-        const int64_t ldb_c = 2 * int64_t(ldc);
-        const int64_t off0 = (row0 + wm * WM) * ldb_c + 2 * (col0 + wn * WN);
-        const int fc = (lane >> 4) * 4;  // the lane's first column in a 16 x 16 tile
+    // staged through the operand buffers, in two halves of 32 rows per wave; the training
+    // forward stages its pre-activations (P) first and then its outputs
+    static_assert(WN * 2 == kStgRowB, "staging");
+    uint8_t *const stg = St0 + w * (32 * kStgStrideB);
+    const int64_t ldb_c = 2 * int64_t(ldc);
+    const int64_t off0 = (row0 + wm * WM) * ldb_c + 2 * (col0 + wn * WN);
+    const int fc = (lane >> 4) * 4;  // the lane's first column in a 16 x 16 tile
 #pragma unroll
-        for (int hf = 0; hf < 2; ++hf) {
-            floatx4 v[TN][2];
+    for (int hf = 0; hf < 2; ++hf) {
+        floatx4 v[TN][2];
 #pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                const floatx4 bc = (EPI == kEpiGeluGrad)
-                                       ? floatx4{0.f, 0.f, 0.f, 0.f}
-                                       : *reinterpret_cast<const floatx4 *>(bias + col0 + wn * WN + j * 16 + fc);
+        for (int j = 0; j < TN; ++j) {
+            const floatx4 bc = (EPI == kEpiGeluGrad)
+                                   ? floatx4{0.f, 0.f, 0.f, 0.f}
+                                   : *reinterpret_cast<const floatx4 *>(bias + col0 + wn * WN + j * 16 + fc);
 #pragma unroll
-                for (int ii = 0; ii < 2; ++ii) v[j][ii] = acc[2 * hf + ii][j] + bc;
-            }
-            if constexpr (EPI == kEpiGeluSave) {
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-#pragma unroll
-                    for (int ii = 0; ii < 2; ++ii)
-                        *reinterpret_cast<bf16x4 *>(stg + (ii * 16 + fr) * kStgStrideB + 2 * (j * 16 + fc)) =
-                            to_bf16x4(v[j][ii]);
-                stage_flush<32>(stg, reinterpret_cast<uint8_t *>(P) + off0 + hf * 32 * ldb_c, ldb_c, lane);
-            }
+            for (int ii = 0; ii < 2; ++ii) v[j][ii] = acc[2 * hf + ii][j] + bc;
+        }
+        if constexpr (EPI == kEpiGeluSave) {
 #pragma unroll
             for (int j = 0; j < TN; ++j)
 #pragma unroll
-                for (int ii = 0; ii < 2; ++ii) {
-                    floatx4 x = v[j][ii];
-                    if constexpr (EPI == kEpiGelu) {
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) x[r] = gelu_tab(x[r], Ptab);
-                    } else if constexpr (EPI == kEpiGeluSave) {
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) x[r] = gelu_erfc(x[r]);
-                    } else {
-                        const int64_t row = row0 + wm * WM + (2 * hf + ii) * 16 + fr;
-                        const bf16x4 pv =
-                            *reinterpret_cast<const bf16x4 *>(P + row * ldc + col0 + wn * WN + j * 16 + fc);
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) x[r] *= gelu_grad(float(pv[r]));
-                    }
+                for (int ii = 0; ii < 2; ++ii)
                     *reinterpret_cast<bf16x4 *>(stg + (ii * 16 + fr) * kStgStrideB + 2 * (j * 16 + fc)) =
-                        to_bf16x4(x);
+                        to_bf16x4(v[j][ii]);
+            stage_flush<32>(stg, reinterpret_cast<uint8_t *>(P) + off0 + hf * 32 * ldb_c, ldb_c, lane);
+        }
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int ii = 0; ii < 2; ++ii) {
+                floatx4 x = v[j][ii];
+                if constexpr (EPI == kEpiGelu) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) x[r] = gelu_tab(x[r], Ptab);
+                } else if constexpr (EPI == kEpiGeluSave) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) x[r] = gelu_erfc(x[r]);
+                } else {
+                    const int64_t row = row0 + wm * WM + (2 * hf + ii) * 16 + fr;
+                    const bf16x4 pv =
+                        *reinterpret_cast<const bf16x4 *>(P + row * ldc + col0 + wn * WN + j * 16 + fc);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) x[r] *= gelu_grad(float(pv[r]));
                 }
-            stage_flush<32>(stg, reinterpret_cast<uint8_t *>(C) + off0 + hf * 32 * ldb_c, ldb_c, lane);
-        }
-        return;
-    }
-    // the linear epilogue (bias only) stores in the MFMA layout
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-        const int col = col0 + wn * WN + j * 16 + (lane >> 4) * 4;
-        const floatx4 bc = *reinterpret_cast<const floatx4 *>(bias + col);
-#pragma unroll
-        for (int i = 0; i < TM; ++i) {
-            const int64_t row = row0 + wm * WM + i * 16 + fr;
-            const int64_t off = row * ldc + col;
-            const floatx4 v = acc[i][j] + bc;
-            *reinterpret_cast<bf16x4 *>(C + off) = to_bf16x4(v);
-        }
+                *reinterpret_cast<bf16x4 *>(stg + (ii * 16 + fr) * kStgStrideB + 2 * (j * 16 + fc)) =
+                    to_bf16x4(x);
+            }
+        stage_flush<32>(stg, reinterpret_cast<uint8_t *>(C) + off0 + hf * 32 * ldb_c, ldb_c, lane);
     }
 }
 
@@ -323,6 +368,17 @@ __device__ __forceinline__ uint32_t to_fp8x4(float a, float b, float c, float d)
     return uint32_t(v);
 }
 
+// E4M3FN bytes of four values of a block with largest magnitude m and scale factor sc.  With a finite m the
+// scale keeps every scaled value within 448 (a NaN value stays NaN through the conversion), so the
+// range rule has nothing to do.
+__device__ __forceinline__ uint32_t fp8_word(floatx4 f, float m, float sc) {
+    if (m <= 3.40282347e38f) {
+        const int v = __builtin_amdgcn_cvt_pk_fp8_f32(f[0] * sc, f[1] * sc, 0, false);
+        return uint32_t(__builtin_amdgcn_cvt_pk_fp8_f32(f[2] * sc, f[3] * sc, v, true));
+    }
+    return to_fp8x4(f[0] * sc, f[1] * sc, f[2] * sc, f[3] * sc);
+}
+
 // FP8 output of a layer whose result feeds an FP8 layer, for a wave that owns whole 32-column
 // blocks: v0 and v1 are the GELU outputs of the 16 x 16 tiles 2q and 2q + 1 of a 16-row tile
 // (lane l: row l % 16, columns 4 (l / 16) + r of each), so a block's 32 values of a row lie with
@@ -347,17 +403,8 @@ __device__ __forceinline__ void quant_fp8_block(floatx4 v0, floatx4 v1, uint8_t 
     m = fmaxf(m, __shfl_xor(m, 32));
     const int e = fp8_scale_exp(m);
     const float sc = ldexpf(1.0f, -e);
-    if (m <= 3.40282347e38f) {
-        // a finite block maximum: the scale keeps every scaled value within 448 (a NaN value
-        // stays NaN through the conversion), so the range rule has nothing to do
-        int v = __builtin_amdgcn_cvt_pk_fp8_f32(f[0] * sc, f[1] * sc, 0, false);
-        w0 = uint32_t(__builtin_amdgcn_cvt_pk_fp8_f32(f[2] * sc, f[3] * sc, v, true));
-        v = __builtin_amdgcn_cvt_pk_fp8_f32(f[4] * sc, f[5] * sc, 0, false);
-        w1 = uint32_t(__builtin_amdgcn_cvt_pk_fp8_f32(f[6] * sc, f[7] * sc, v, true));
-    } else {
-        w0 = to_fp8x4(f[0] * sc, f[1] * sc, f[2] * sc, f[3] * sc);
-        w1 = to_fp8x4(f[4] * sc, f[5] * sc, f[6] * sc, f[7] * sc);
-    }
+    w0 = fp8_word(floatx4{f[0], f[1], f[2], f[3]}, m, sc);
+    w1 = fp8_word(floatx4{f[4], f[5], f[6], f[7]}, m, sc);
     if (g == 0) S[row * sst + c0 / kFp8Block] = uint8_t(127 + e);
 }
 
@@ -481,8 +528,10 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_shallow_kernel(const bf16_t 
     }
 }
 
-// FP8 layer on the block-scaled matrix cores: the tiling of gemm_kernel (128 x 160 block tile,
-// 2 x 2 waves of 64 x 80) with 128-deep stages of E4M3FN bytes.  In a 16x16x128 product with
+// FP8 layer on the block-scaled matrix cores: the tiling and staging of gemm_kernel (128 x 160 block tile,
+// 2 x 2 waves of 64 x 80) with 128-deep stages of E4M3FN bytes; 65,536 rows, 3200 -> 1600 (FP8 output) and
+// 1600 -> 800: 570 and 174 us staged through registers with 144-byte LDS rows (a third of the LDS time was bank
+// conflicts) and waves of 32 x 160 for the FP8 output, 441 and 149 us so.  In a 16x16x128 product with
 // 8-bit operands, lane l supplies row l % 16 of its operand at the stage's inputs 16 g .. 16 g + 15
 // (bytes 0-15) and 64 + 16 g .. 64 + 16 g + 15 (bytes 16-31), g = l / 16, and the E8M0 scale of
 // the inputs 32 g .. 32 g + 31 of that row: its two halves lie with lanes g' = 2 (g % 2) and
@@ -491,21 +540,24 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_shallow_kernel(const bf16_t 
 // block g of the stage (the weight row's scale, 127 + wexp, is the same for all blocks).  Inputs
 // at or beyond K (the last stage of a K that is not a multiple of 128) are zeros with scale 2^0.
 typedef int i32x8 __attribute__((ext_vector_type(8)));
-constexpr int KD8 = 128, LDK8 = KD8 + 16;  // stage depth and LDS row stride in bytes
+constexpr int KD8 = 128;  // stage depth
 
-template <bool Q8>
-__global__ __launch_bounds__(kThreads, 2) void gemm_fp8_kernel(const uint8_t *__restrict__ A8, int lda,
+template <bool Q8, int NST>
+__global__ __launch_bounds__(kThreads, NST == 2 ? 2 : 1) void gemm_fp8_kernel(const uint8_t *__restrict__ A8, int lda,
                                                            const uint8_t *__restrict__ SA, int sst,
                                                            const uint8_t *__restrict__ W8, int ldb,
                                                            const int32_t *__restrict__ wexp,
                                                            const float *__restrict__ bias, bf16_t *__restrict__ C,
                                                            int ldc, uint8_t *__restrict__ SC, int sstc, int K,
                                                            int n_tiles_n) {
-    constexpr int WMq = Q8 ? 32 : WM, WNq = Q8 ? 160 : WN, TMq = WMq / 16, TNq = WNq / 16;
-    // the operand stages; after the stage loop the epilogue stages its outputs here
-    __shared__ __attribute__((aligned(16))) uint8_t AB8[(BM + BN) * LDK8];
-    uint8_t *const As = AB8, *const Bs = AB8 + BM * LDK8;
-    __shared__ uint32_t Ss[BM];
+    constexpr int kNa = BM / 32, kNb = BN / 32;  // load instructions of a wave per stage (8 rows each)
+    // the operand stages, each followed by the four block scales of its A rows as a word per row; after the
+    // stage loop the epilogue stages its outputs in the first
+    constexpr int kScOff = kStageB, kSt = kStageB + 4 * BM;
+    __shared__ __attribute__((aligned(1024))) uint8_t St0[kSt];
+    __shared__ __attribute__((aligned(1024))) uint8_t St1[kSt];
+    __shared__ __attribute__((aligned(1024))) uint8_t St2[NST > 2 ? kSt : 16];
+    __shared__ __attribute__((aligned(1024))) uint8_t St3[NST > 2 ? kSt : 16];
     __shared__ __attribute__((aligned(16))) float Ptab[kPhiLdsFloats];
 
     const int nb = gridDim.x, b = blockIdx.x;
@@ -514,138 +566,155 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_fp8_kernel(const uint8_t *__
     const int64_t row0 = int64_t(tile_m) * BM;
     const int col0 = tile_n * BN;
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-    const int wm = Q8 ? w : w >> 1, wn = Q8 ? 0 : w & 1;
+    const int wm = w >> 1, wn = w & 1;
     const int fr = lane & 15, fg = lane >> 4;
 
-    // 16-byte chunks: A BM*KD8/16 = 1024 (4 per thread), W BN*KD8/16 = 1280 (5 per thread)
-    constexpr int kCh = KD8 / 16;
-    constexpr int kAPer = BM * kCh / kThreads, kBPer = BN * kCh / kThreads;
-    u32x4 ra[kAPer], rb[kBPer];
-    uint32_t rs = 0;
-    const u32x4 z4 = {0u, 0u, 0u, 0u};
-    auto load = [&](int k0) {
-        if (k0 + KD8 <= K) {
-            // a whole stage within K (the same for the block): no guards, and the four block
-            // scales of a row as one little-endian word (4-byte aligned: sst % 16 = 0, k0 % 128 = 0)
+    // loads as in gemm_kernel, and one of 64 rows' scales; the last stage of a K that is not a multiple of 128
+    // gets zeros from ordinary LDS stores at its inputs beyond K
+    const int lr = lane >> 3, lc = (lane & 7) ^ lr, wu = __builtin_amdgcn_readfirstlane(w);
+    const int ra = 8 * kNa * wu, rb = 8 * kNb * wu;
+    const int ws = 64 * (wu % 2);  // the rows whose scales this wave loads
+    const int sta = 8 * lda, stb = 8 * ldb;  // bytes of 8 rows
+    const __amdgpu_buffer_rsrc_t ba = buffer_of(A8 + (row0 + ra) * lda, kNa * sta),
+                                 bb = buffer_of(W8 + int64_t(col0 + rb) * ldb, kNb * stb),
+                                 bs = buffer_of(SA + (row0 + ws) * sst, 64 * sst);
+    const int oa = lr * lda + lc * 16, ob = lr * ldb + lc * 16, os = lane * sst;
+    auto load = [&](int s, uint8_t *st) {
+        uint8_t *pa = st + ra * kStRowB, *pb = st + kABytes + rb * kStRowB;
+        const bool in = lc * 16 < K - KD8 * s;
+        dma_rows<kNa>(ba, in ? oa : kNoRow, KD8 * s, sta, pa);
+        dma_rows<kNb>(bb, in ? ob : kNoRow, KD8 * s, stb, pb);
+        if (K - KD8 * s > 0 && !in) {
+            const u32x4 z = {0u, 0u, 0u, 0u};
 #pragma unroll
-            for (int i = 0; i < kAPer; ++i) {
-                const int c = t + i * kThreads, r = c / kCh, k = k0 + (c % kCh) * 16;
-                ra[i] = *reinterpret_cast<const u32x4 *>(A8 + (row0 + r) * lda + k);
-            }
+            for (int i = 0; i < kNa; ++i) *reinterpret_cast<u32x4 *>(pa + i * 1024 + lane * 16) = z;
 #pragma unroll
-            for (int i = 0; i < kBPer; ++i) {
-                const int c = t + i * kThreads, r = c / kCh, k = k0 + (c % kCh) * 16;
-                rb[i] = *reinterpret_cast<const u32x4 *>(W8 + int64_t(col0 + r) * ldb + k);
-            }
-            if (t < BM) rs = *reinterpret_cast<const uint32_t *>(SA + (row0 + t) * sst + k0 / kFp8Block);
-            return;
+            for (int i = 0; i < kNb; ++i) *reinterpret_cast<u32x4 *>(pb + i * 1024 + lane * 16) = z;
         }
-#pragma unroll
-        for (int i = 0; i < kAPer; ++i) {
-            const int c = t + i * kThreads, r = c / kCh, k = k0 + (c % kCh) * 16;
-            ra[i] = (k < K) ? *reinterpret_cast<const u32x4 *>(A8 + (row0 + r) * lda + k) : z4;
-        }
-#pragma unroll
-        for (int i = 0; i < kBPer; ++i) {
-            const int c = t + i * kThreads, r = c / kCh, k = k0 + (c % kCh) * 16;
-            rb[i] = (k < K) ? *reinterpret_cast<const u32x4 *>(W8 + int64_t(col0 + r) * ldb + k) : z4;
-        }
-        // the four block scales of a row for this stage; 127 (2^0) for blocks at or beyond K
-        if (t < BM) {
-            const uint8_t *sp = SA + (row0 + t) * sst + k0 / kFp8Block;
-            uint32_t v = 0;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) v |= uint32_t((k0 + q * kFp8Block < K) ? sp[q] : 127) << (8 * q);
-            rs = v;
-        }
-    };
-    auto store = [&]() {
-#pragma unroll
-        for (int i = 0; i < kAPer; ++i) {
-            const int c = t + i * kThreads;
-            *reinterpret_cast<u32x4 *>(As + (c / kCh) * LDK8 + (c % kCh) * 16) = ra[i];
-        }
-#pragma unroll
-        for (int i = 0; i < kBPer; ++i) {
-            const int c = t + i * kThreads;
-            *reinterpret_cast<u32x4 *>(Bs + (c / kCh) * LDK8 + (c % kCh) * 16) = rb[i];
-        }
-        if (t < BM) Ss[t] = rs;
+        // (a word is 4-byte aligned, sst % 16 = 0, and inside the row's sst bytes)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(bs, (lds_void *)(st + kScOff + 4 * ws), 4,
+                                                 KD8 * s < K ? os : kNoRow, 4 * s, 0, 0);
     };
 
-    int sw[TNq];  // E8M0 scale of the weight row each lane supplies
+    int sw[TN];  // E8M0 scale of the weight row each lane supplies
 #pragma unroll
-    for (int j = 0; j < TNq; ++j) sw[j] = 127 + wexp[col0 + wn * WNq + j * 16 + fr];
-    floatx4 acc[TMq][TNq];
+    for (int j = 0; j < TN; ++j) sw[j] = 127 + wexp[col0 + wn * WN + j * 16 + fr];
+    floatx4 acc[TM][TN];
 #pragma unroll
-    for (int i = 0; i < TMq; ++i)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < TNq; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < TN; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
 
-    load(0);
-    copy_phi_table(Ptab, t);  // visible after the stage loop's first barrier
-    for (int k0 = 0; k0 < K; k0 += KD8) {
-        __syncthreads();
-        store();
-        __syncthreads();
-        if (k0 + KD8 < K) load(k0 + KD8);
+    const int fa = (wm * WM + fr) * kStRowB, fb = kABytes + (wn * WN + fr) * kStRowB;
+    const int c0 = (fg ^ (fr & 7)) * 16, c1 = ((4 + fg) ^ (fr & 7)) * 16;
+    copy_phi_table(Ptab, t);  // visible after the stage loop's barriers
+    stage_loop<NST, kNa + kNb + 1>((K + KD8 - 1) / KD8, St0, St1, St2, St3, load, [&](int s, const uint8_t *st) {
         auto frag = [&](const uint8_t *row) {
-            const u32x4 lo = *reinterpret_cast<const u32x4 *>(row + fg * 16);
-            const u32x4 hi = *reinterpret_cast<const u32x4 *>(row + 64 + fg * 16);
+            const u32x4 lo = *reinterpret_cast<const u32x4 *>(row + c0);
+            const u32x4 hi = *reinterpret_cast<const u32x4 *>(row + c1);
             return i32x8{int(lo[0]), int(lo[1]), int(lo[2]), int(lo[3]), int(hi[0]), int(hi[1]), int(hi[2]), int(hi[3])};
         };
-        // the activation fragments (fewer than the weight ones) held, the weight fragments one at a time
-        i32x8 af[TMq];
-        int sa[TMq];
+        // this lane's block of a row's scale word, 2^0 where the block is at or beyond K
+        const bool in = s * KD8 + fg * kFp8Block < K;
+        const uint32_t mask = in ? 0xffu : 0u, fill = in ? 0u : 127u;
+        // the activation fragments (fewer than the weight ones) held, the weight fragments a few at a time
+        i32x8 af[TM];
+        int sa[TM];
 #pragma unroll
-        for (int i = 0; i < TMq; ++i) {
-            const int r = wm * WMq + i * 16 + fr;
-            af[i] = frag(As + r * LDK8);
-            sa[i] = int((Ss[r] >> (8 * fg)) & 0xffu);
+        for (int i = 0; i < TM; ++i) {
+            af[i] = frag(st + fa + i * 16 * kStRowB);
+            const uint32_t v = *reinterpret_cast<const uint32_t *>(st + kScOff + 4 * (wm * WM + i * 16 + fr));
+            sa[i] = int(((v >> (8 * fg)) & mask) | fill);
         }
 #pragma unroll
-        for (int j = 0; j < TNq; ++j) {
-            const i32x8 wf = frag(Bs + (wn * WNq + j * 16 + fr) * LDK8);
+        for (int j = 0; j < TN; ++j) {
+            // keeps the scheduler from moving all the weight fragments up, which spills
+            if (j % 2 == 0) __builtin_amdgcn_sched_barrier(0);
+            const i32x8 wf = frag(st + fb + j * 16 * kStRowB);
 #pragma unroll
-            for (int i = 0; i < TMq; ++i)
+            for (int i = 0; i < TM; ++i)
                 acc[i][j] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(wf, af[i], acc[i][j], 0, 0, 0, sw[j], 0, sa[i]);
         }
-    }
+    });
 
-    // outputs staged through the operand buffers: the FP8 copy as one stage of 32 rows x 160
-    // bytes per wave, bf16 outputs in two halves of 32 rows x 80 values
-    static_assert(4 * 32 * kStgStrideB <= (BM + BN) * LDK8, "staging fits the operand buffers");
-    __syncthreads();  // every wave has read its last operand fragments
-    uint8_t *const stg = AB8 + w * (32 * kStgStrideB);
     if constexpr (Q8) {
+        // A wave's 80 columns are two 32-column blocks and half of the block that it shares with the other wave
+        // of its rows (the last half of wave 0's, the first of wave 1's columns): the two exchange
+        // that block's row maxima through LDS.  The FP8 rows (160 bytes of both waves) are staged by row.
+        static_assert(kStgRowB == 2 * WN, "staging");
+        float *const Mx = reinterpret_cast<float *>(St1);  // [2][BM]
+        uint8_t *const stg = St0 + wm * (WM * kStgStrideB);
+        float mx[TM][TN];
 #pragma unroll
-        for (int q = 0; q < TNq / 2; ++q) {
-            const floatx4 b0 = *reinterpret_cast<const floatx4 *>(bias + col0 + 32 * q + fg * 4);
-            const floatx4 b1 = *reinterpret_cast<const floatx4 *>(bias + col0 + 32 * q + 16 + fg * 4);
+        for (int j = 0; j < TN; ++j) {
+            const floatx4 bc = *reinterpret_cast<const floatx4 *>(bias + col0 + wn * WN + j * 16 + fg * 4);
 #pragma unroll
-            for (int i = 0; i < TMq; ++i) {
-                floatx4 v0 = acc[i][2 * q] + b0, v1 = acc[i][2 * q + 1] + b1;
+            for (int i = 0; i < TM; ++i) {
+                floatx4 v = acc[i][j] + bc;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) v[r] = gelu_tab(v[r], Ptab);
+                const bf16x4 h = to_bf16x4(v);
+                float m = 0.0f;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    v0[r] = gelu_tab(v0[r], Ptab);
-                    v1[r] = gelu_tab(v1[r], Ptab);
+                    acc[i][j][r] = float(h[r]);
+                    m = fmaxf(m, fabsf(acc[i][j][r]));
                 }
-                uint32_t w0, w1;
-                quant_fp8_block(v0, v1, SC, row0 + wm * WMq + i * 16 + fr, sstc, col0 + 32 * q, fg, w0, w1);
-                uint8_t *p = stg + (i * 16 + fr) * kStgStrideB + 32 * q + 4 * fg;
-                *reinterpret_cast<uint32_t *>(p) = w0;
-                *reinterpret_cast<uint32_t *>(p + 16) = w1;
+                m = fmaxf(m, __shfl_xor(m, 16));
+                mx[i][j] = fmaxf(m, __shfl_xor(m, 32));
             }
         }
-        stage_flush<32>(stg, reinterpret_cast<uint8_t *>(C) + (row0 + wm * WMq) * int64_t(ldc) + col0, ldc, lane);
+        if (fg == 0) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i) {
+                const int row = wm * WM + i * 16 + fr;
+                if (wn)
+                    Mx[BM + row] = mx[i][0];
+                else
+                    Mx[row] = mx[i][TN - 1];
+            }
+        }
+        __syncthreads();
+        // columns of 16-column tile j of this wave within the panel: block (5 wn + j) / 2
+        auto finish = [&](auto WN_) {
+            constexpr int kW = decltype(WN_)::value;
+#pragma unroll
+            for (int i = 0; i < TM; ++i) {
+                const int row = wm * WM + i * 16 + fr;
+                const float other = Mx[(1 - kW) * BM + row];
+#pragma unroll
+                for (int j = 0; j < TN; ++j) {
+                    const int c16 = TN * kW + j;  // in 16s, from the panel's first column
+                    const int jp = j + (c16 % 2 ? -1 : 1);
+                    float m = fmaxf(mx[i][j], other);
+                    if (jp >= 0 && jp < TN) m = fmaxf(mx[i][j], mx[i][jp]);
+                    const int e = fp8_scale_exp(m);
+                    *reinterpret_cast<uint32_t *>(stg + (i * 16 + fr) * kStgStrideB + c16 * 16 + 4 * fg) =
+                        fp8_word(acc[i][j], m, ldexpf(1.0f, -e));
+                    // the block's scale, from the wave that holds its first half
+                    if (c16 % 2 == 0 && fg == 0)
+                        SC[(row0 + row) * sstc + (col0 + c16 * 16) / kFp8Block] = uint8_t(127 + e);
+                }
+            }
+        };
+        if (wn)
+            finish(std::integral_constant<int, 1>{});
+        else
+            finish(std::integral_constant<int, 0>{});
+        __syncthreads();
+        // half of the rows for each of the two waves
+            stage_flush<WM / 2>(stg + wn * (WM / 2 * kStgStrideB),
+                                reinterpret_cast<uint8_t *>(C) + (row0 + wm * WM + wn * (WM / 2)) * int64_t(ldc) + col0,
+                                ldc, lane);
     } else {
+        uint8_t *const stg = St0 + w * (32 * kStgStrideB);
         const int64_t ldb_c = 2 * int64_t(ldc);
-        uint8_t *const dst = reinterpret_cast<uint8_t *>(C) + (row0 + wm * WMq) * ldb_c + 2 * (col0 + wn * WNq);
+        uint8_t *const dst = reinterpret_cast<uint8_t *>(C) + (row0 + wm * WM) * ldb_c + 2 * (col0 + wn * WN);
 #pragma unroll
         for (int hf = 0; hf < 2; ++hf) {
 #pragma unroll
-            for (int j = 0; j < TNq; ++j) {
-                const floatx4 bc = *reinterpret_cast<const floatx4 *>(bias + col0 + wn * WNq + j * 16 + fg * 4);
+            for (int j = 0; j < TN; ++j) {
+                const floatx4 bc = *reinterpret_cast<const floatx4 *>(bias + col0 + wn * WN + j * 16 + fg * 4);
 #pragma unroll
                 for (int ii = 0; ii < 2; ++ii) {
                     floatx4 v = acc[2 * hf + ii][j] + bc;
@@ -879,6 +948,13 @@ void launch_rows(int tile, const bf16_t *A, int lda, const bf16_t *B, int ldb, c
                        dim3(64), 0, stream, A, lda, B, ldb, bias, C, ldc, S, sst, K, tn, P);
 }
 
+// Four stages in LDS and one block per CU for grids of at most one block per CU, where only the stages in flight
+// hide the loads; otherwise two stages and two blocks per CU, which hide each other's loads and
+// epilogues.  N x K, rows (tiles), two / four stages in us: 800 x 1600, 4,096 (160) 26.0 / 24.2;
+// 1600 x 3200, 2,048 (160) 45 / 40; 400 x 800, 8,192 (192) 17.8 / 17.1; beyond 256 tiles the four-stage
+// form would take two rounds.
+bool deep_stages(int64_t tiles) { return tiles <= 256; }
+
 // the shallow-reduction layer (K = 32 or 64, shapes checked by the caller): about two blocks per
 // CU, each on one 160-column panel and every G-th row tile; S != nullptr: FP8 output (C holds the
 // E4M3FN bytes with row stride ldc, S the block scales with row stride sst)
@@ -924,16 +1000,16 @@ df_status launch_gemm_bf16_epi(const bf16_t *A, int lda, const bf16_t *B, int ld
                                hipStream_t stream) {
     if (rows < 0 || rows > M || M % BM || N % BN || K % BK || K <= 0 || lda % 8 || ldb % 8)
         return fail(DF_E_INVALID, "gemm: shapes must be multiples of the tile sizes");
-    // the outputs of every epilogue but the linear one are written as 16-byte row pieces
-    if (epi != GemmEpi::linear && ((reinterpret_cast<uintptr_t>(C) & 15) || ldc % 8 ||
-                                   (epi == GemmEpi::gelu_save && (reinterpret_cast<uintptr_t>(P) & 15))))
+    // the outputs are written as 16-byte row pieces
+    if ((reinterpret_cast<uintptr_t>(C) & 15) || ldc % 8 ||
+        (epi == GemmEpi::gelu_save && (reinterpret_cast<uintptr_t>(P) & 15)))
         return fail(DF_E_INVALID, "gemm: the output rows must be 16-byte aligned");
     if ((epi == GemmEpi::gelu_save || epi == GemmEpi::gelu_grad) && !P)
         return fail(DF_E_INVALID, "gemm: the epilogue needs the pre-activation array");
     if (M == 0) return DF_OK;
     const int64_t tiles = (M / BM) * (N / BN);
     if (tiles > 0x7fffffff) return fail(DF_E_UNSUPPORTED, "gemm: too many tiles");
-    if (const int tile = epi == GemmEpi::linear ? 0 : rows_tile(rows, N, K, false, false)) {
+    if (const int tile = rows_tile(rows, N, K, false, false)) {
         if (rows == 0) return DF_OK;
         if (epi == GemmEpi::gelu)
             launch_rows<kEpiGelu, false>(tile, A, lda, B, ldb, bias, C, ldc, nullptr, 0, rows, N, K, nullptr, stream);
@@ -948,24 +1024,29 @@ df_status launch_gemm_bf16_epi(const bf16_t *A, int lda, const bf16_t *B, int ld
     if (epi == GemmEpi::gelu && (K == 32 || K == 64))
         return launch_shallow(A, lda, B, ldb, bias, C, ldc, nullptr, 0, M, N, K, stream);
     const dim3 g = dim3(unsigned(tiles)), b = dim3(kThreads);
-    const bool deep = K % 64 == 0;
-#define DF_GEMM(E)                                                                                              \
-    if (deep)                                                                                                   \
-        hipLaunchKernelGGL((gemm_kernel<E, 64>), g, b, 0, stream, A, lda, B, ldb, bias, C, ldc, K, N / BN, P);  \
-    else                                                                                                        \
-        hipLaunchKernelGGL((gemm_kernel<E, 32>), g, b, 0, stream, A, lda, B, ldb, bias, C, ldc, K, N / BN, P);
+#define DF_GEMM(E, NST) \
+    hipLaunchKernelGGL((gemm_kernel<E, NST>), g, b, 0, stream, A, lda, B, ldb, bias, C, ldc, K, N / BN, P)
+    const bool deep = deep_stages(tiles);
     switch (epi) {
         case GemmEpi::gelu:
-            DF_GEMM(kEpiGelu)
-            break;
-        case GemmEpi::linear:
-            DF_GEMM(kEpiLinear)
+            if (deep)
+                DF_GEMM(kEpiGelu, 4);
+            else
+                DF_GEMM(kEpiGelu, 2);
             break;
         case GemmEpi::gelu_save:
-            DF_GEMM(kEpiGeluSave)
+            if (K <= 64)
+                DF_GEMM(kEpiGeluSave, 1);
+            else if (deep)
+                DF_GEMM(kEpiGeluSave, 4);
+            else
+                DF_GEMM(kEpiGeluSave, 2);
             break;
         case GemmEpi::gelu_grad:
-            DF_GEMM(kEpiGeluGrad)
+            if (deep)
+                DF_GEMM(kEpiGeluGrad, 4);
+            else
+                DF_GEMM(kEpiGeluGrad, 2);
             break;
     }
 #undef DF_GEMM
@@ -1013,12 +1094,21 @@ df_status launch_gemm_fp8(const uint8_t *A8, int lda, const uint8_t *S, int sst,
         else
             hipLaunchKernelGGL((gemm_fp8_rows_kernel<false, 2, 2>), g, b, 0, stream, A8, lda, S, sst, W8, ldb,
                                wexp, bias, C, ldc, SC, sstc, K, tn);
-    } else if (SC)
-        hipLaunchKernelGGL(gemm_fp8_kernel<true>, dim3(unsigned(tiles)), dim3(kThreads), 0, stream, A8, lda, S, sst, W8,
-                           ldb, wexp, bias, C, ldc, SC, sstc, K, N / BN);
-    else
-        hipLaunchKernelGGL(gemm_fp8_kernel<false>, dim3(unsigned(tiles)), dim3(kThreads), 0, stream, A8, lda, S, sst,
-                           W8, ldb, wexp, bias, C, ldc, SC, sstc, K, N / BN);
+    } else {
+        const dim3 g = dim3(unsigned(tiles)), b = dim3(kThreads);
+#define DF_GEMM8(Q, W)                                                                                              \
+    hipLaunchKernelGGL((gemm_fp8_kernel<Q, W>), g, b, 0, stream, A8, lda, S, sst, W8, ldb, wexp, bias, C, ldc, SC, sstc, \
+                       K, N / BN)
+        if (SC && !deep_stages(tiles))
+            DF_GEMM8(true, 2);
+        else if (SC)
+            DF_GEMM8(true, 4);
+        else if (!deep_stages(tiles))
+            DF_GEMM8(false, 2);
+        else
+            DF_GEMM8(false, 4);
+#undef DF_GEMM8
+    }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(DF_E_HIP, std::string("gemm fp8 launch: ") + hipGetErrorString(e));
     return DF_OK;
