@@ -60,6 +60,9 @@ df_status launch_chem_step(const MechDev &m, const StepArgs &a, int mapping, con
     // lanes.  Larger mechanisms: mapping 0 picks 16 lanes per cell whenever a kernel is compiled for
     // K, and with the cost order (and reaction slots that divide in two) 32 lanes for the head of
     // the order (mapping 5), whose stiffest cells then finish sooner
+    // mapping 3, and 0 for the species counts without a smaller kernel: eight waves per cell where
+    // the mechanism fits their threads, else one
+    if (mapping == 3 && chem_block_supported(m)) return launch_chem_block(m, a, cidx, dcount, stream);
     if (mapping == 3) return launch_chem_wave(m, a, cidx, dcount, stream);
     if (mapping != 1 && chem_cell_supported(m))
         return launch_chem_cell(m, a, CellQueue{cidx, dcount, nullptr, nullptr, nullptr, 0}, stream);
@@ -74,6 +77,7 @@ df_status launch_chem_step(const MechDev &m, const StepArgs &a, int mapping, con
         DF_CHEM_SPECIES_LIST(DF_CASE)
 #undef DF_CASE
         default:
+            if (mapping == 0 && chem_block_supported(m)) return launch_chem_block(m, a, cidx, dcount, stream);
             if (mapping == 0 && chem_wave_supported(m)) return launch_chem_wave(m, a, cidx, dcount, stream);
             return fail(DF_E_UNSUPPORTED, "df_chem_step: no compiled kernel for " + std::to_string(m.K) + " species");
     }

@@ -77,6 +77,7 @@ struct MechDev {
     // the per-species reaction lists packed (j, nu), species k at wlo[k] <= e < wlo[k + 1]
     const int *wlo;     // [K + 1]
     const int *wlp;
+    int wnl, wnd, wtb;  // entries of wlp and wdp; falloff and third-body reactions (stored first)
     // the dense third-body terms: row k gains sum over wdo[k] <= e < wdo[k + 1] of
     // nu G_j eff_jl, (j, nu) packed in wdp[e]
     const int *wdo;      // [K + 1]
@@ -196,6 +197,11 @@ df_status validate_chem_opts(const df_chem_opts &o);
 bool chem_wave_supported(const MechDev &m);
 df_status launch_chem_wave(const MechDev &m, const StepArgs &a, const int32_t *cidx, const int32_t *dcount,
                            hipStream_t stream);
+
+// one block of eight waves per cell for hydrocarbon-size mechanisms (df_chem_block.hip)
+bool chem_block_supported(const MechDev &m);
+df_status launch_chem_block(const MechDev &m, const StepArgs &a, const int32_t *cidx, const int32_t *dcount,
+                            hipStream_t stream);
 
 // cooperative integrator (df_chem_coop.hip): 16 lanes per cell (halves = 1), or 32 (halves = 2, where
 // the reaction slots divide between two halves and no tape is written), for the species counts

@@ -724,6 +724,9 @@ df_status df_mech_load(const char *path, int32_t device, df_mech **out) {
     m->dev.wrc = I(18);
     m->dev.wlo = I(19);
     m->dev.wlp = I(20);
+    m->dev.wnl = int(wt.lp.size());
+    m->dev.wnd = int(wt.dp.size());
+    m->dev.wtb = int(std::count_if(m->host.type.begin(), m->host.type.end(), [](int t) { return t != 0; }));
     m->dev.wdo = I(21);
     m->dev.wdp = I(22);
     m->dev.xd = D(23);
