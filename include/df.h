@@ -77,7 +77,9 @@ typedef struct {
     int32_t max_steps; /* attempted sub-steps per cell and call, default 100000 */
     int32_t mapping;   /* work mapping of the static schedule: 0 (default) automatic, 1 one cell
                           per lane, 2 sixteen lanes per cell (species count <= 15), 3 one
-                          wavefront (64 lanes) per cell (species count <= 63), 4 thirty-two
+                          wavefront (64 lanes) per cell (species count <= 63), or one block of
+                          eight for 53 species where the reactions fit its threads (up to 64
+                          third-body and falloff ones and 80 KB of LDS), 4 thirty-two
                           lanes per cell (as 2, the second 16 lanes taking half of the rate
                           constants: a shorter sub-step for stiff cells, half the cells per wave;
                           16 lanes where the reaction slots do not divide in two), 5 thirty-two
@@ -85,7 +87,7 @@ typedef struct {
                           whose sub-step chains set the launch's time) and sixteen for the rest
                           (needs the workspace, which holds the order; as 2 without it);
                           automatic takes 5 where the reaction slots divide in two, else 16 lanes,
-                          where compiled, else one cell per lane, else a wavefront.  Where a
+                          where compiled, else one cell per lane, else as 3.  Where a
                           mechanism's rates fit the lanes of one wave (up to 31 reactions, four spare
                           lanes per falloff reaction), automatic, 2, 4 and 5 and the queue
                           schedule all run one wavefront per cell with tables in registers.
@@ -99,7 +101,8 @@ typedef struct {
     int32_t coop_blocks; /* queue schedule: waves that start as 16-lane groups; the others start
                             one cell per lane on the cold cells and then join the groups.
                             0 (default) all resident waves, -1 none, k > 0 k waves (capped at
-                            the resident count); df_chem_autotune picks it */
+                            the resident count); df_chem_autotune picks it; ignored where one
+                            wavefront per cell runs */
 } df_chem_opts;
 
 /* DNN options. */
@@ -324,7 +327,8 @@ df_status df_chem_autotune(const df_mech *mech, int64_t n_cells, int64_t ld, dou
 df_status df_chem_tape_size(const df_mech *mech, int64_t n_cells, int32_t max_substeps, size_t *bytes);
 
 /*
- * df_chem_step (16 lanes per cell, each cell from a fresh start: no sub-step hint, no rr)
+ * df_chem_step (one wavefront per cell where the mechanism fits, else 16 lanes; each cell from a fresh start: no
+ * sub-step hint, no rr)
  * that also records the tape for df_chem_adjoint.
  *   p, T, Y, cell_status, n_steps, opts: as df_chem_step
  *   tape          device memory of df_chem_tape_size(mech, n_cells, max_substeps) bytes,
@@ -356,7 +360,8 @@ df_status df_chem_adjoint_workspace_size(const df_mech *mech, int64_t n_cells, s
  *   lnA_bar_cells [M*ld]         out   per cell, d L / d ln A_j (row j in the mechanism file's
  *                                      reaction order; k_inf's A for falloff rows) (nullable)
  *   lnA_bar [M]                  out   the same summed over cells, in a fixed order (nullable)
- *   workspace     device memory of df_chem_adjoint_workspace_size bytes, 256-byte aligned
+ *   workspace     device memory of df_chem_adjoint_workspace_size bytes, 256-byte aligned (one of only
+ *                 8 M n_cells bytes is accepted too: the sweep then takes the cells by index)
  * Cells without a tape get zero gradients.  Inputs are not modified.  The tape, the seeds and
  * the outputs are caller-owned device memory; nothing is kept after the call.
  * Errors: DF_E_INVALID (null handle/array, n < 0, ld < n, max_substeps < 1, tape or workspace

@@ -569,7 +569,10 @@ __global__ __launch_bounds__(256) void sum_cells_kernel(const double *__restrict
 }
 
 // per-cell ln A adjoints, then the order of the one-wave-per-cell sweep
-size_t adj_ws_bytes(int, int M, int64_t n) { return (size_t(8) * size_t(M) + 4) * size_t(n); }
+// The per-cell ln A gradients, and after them the sweep's cell order.  The order is optional: a workspace of the
+// gradients alone is accepted, and the sweep then takes the cells by index.
+size_t adj_ws_min_bytes(int M, int64_t n) { return size_t(8) * size_t(M) * size_t(n); }
+size_t adj_ws_bytes(int M, int64_t n) { return adj_ws_min_bytes(M, n) + size_t(4) * size_t(n); }
 
 size_t adj_lds_bytes(int K, int M) {
     const size_t N = size_t(K + 1), Ms = size_t(M), Ks = size_t(K);
@@ -681,7 +684,7 @@ extern "C" df_status df_chem_adjoint_workspace_size(const df_mech *mech, int64_t
     using namespace df;
     clear_error();
     if (!mech || !bytes || n_cells < 0) return fail(DF_E_INVALID, "df_chem_adjoint_workspace_size: bad arguments");
-    *bytes = adj_ws_bytes(mech->host.K, mech->host.M, n_cells);
+    *bytes = adj_ws_bytes(mech->host.M, n_cells);
     return DF_OK;
 }
 
@@ -702,7 +705,7 @@ extern "C" df_status df_chem_adjoint(const df_mech *mech, int64_t n_cells, int64
     if (n_cells > 0 && (tape_size < tape_bytes(K, n_cells, max_substeps) ||
                         reinterpret_cast<uintptr_t>(tape) % 256 != 0))
         return fail(DF_E_INVALID, std::string(who) + ": tape smaller than df_chem_tape_size or not 256-byte aligned");
-    if (n_cells > 0 && (ws_bytes < adj_ws_bytes(K, M, n_cells) || reinterpret_cast<uintptr_t>(workspace) % 256 != 0))
+    if (n_cells > 0 && (ws_bytes < adj_ws_min_bytes(M, n_cells) || reinterpret_cast<uintptr_t>(workspace) % 256 != 0))
         return fail(DF_E_INVALID,
                     std::string(who) + ": workspace smaller than df_chem_adjoint_workspace_size or not 256-byte aligned");
     if (!adjoint_supported(mech->dev))
@@ -724,7 +727,11 @@ extern "C" df_status df_chem_adjoint(const df_mech *mech, int64_t n_cells, int64
     df_status st = DF_OK;
     if (sweep_cell_supported(mech->dev)) {
         st = launch_sweep_cell(mech->dev, n_cells, ld, p, a.tape, max_substeps, T_bar, Y_bar, T0_bar, Y0_bar,
-                               lnA_bar_cells, a.wth, reinterpret_cast<int32_t *>(a.wth + int64_t(M) * n_cells), s);
+                               lnA_bar_cells, a.wth,
+                               ws_bytes >= adj_ws_bytes(M, n_cells)
+                                   ? reinterpret_cast<int32_t *>(a.wth + int64_t(M) * n_cells)
+                                   : nullptr,
+                               s);
     } else switch (K) {
 #define DF_CASE(k)                                   \
     case k:                                          \

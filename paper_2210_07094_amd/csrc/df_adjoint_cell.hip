@@ -40,7 +40,7 @@ struct SweepArgs {
     const double *sp;   // species rows
     const double *ad;   // slot lists
     const int *ai;
-    const int32_t *order;  // cells, most sub-steps first
+    int32_t *order;  // cells, most sub-steps first; null: by index
 };
 
 // The cells by decreasing number of sub-steps (the sweep's chains; a late start of a long one would set
@@ -414,7 +414,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1))) void
     constexpr int N = C::N, NI = C::NI;
     extern __shared__ double sh[];
     const int lane = threadIdx.x, r = lane & 15, g = lane >> 4;
-    const int64_t i = a.order[blockIdx.x];
+    const int64_t i = a.order ? int64_t(a.order[blockIdx.x]) : int64_t(blockIdx.x);
     for (int e = lane; e < S::kSize; e += 64) sh[e] = 0.0;
     lds_order();
     for (int e = lane; e < 32 * K; e += 64) {
@@ -522,8 +522,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1))) void
 template <int K, int EL>
 df_status launch_k(const MechDev &m, const SweepArgs &a, hipStream_t s) {
     const Tape tp(K, a.n, a.cap);
-    hipLaunchKernelGGL(sweep_order, dim3(1), dim3(kSortThreads), 0, s, tp.count(a.tape), int(a.n),
-                       const_cast<int32_t *>(a.order));
+    if (a.order)
+        hipLaunchKernelGGL(sweep_order, dim3(1), dim3(kSortThreads), 0, s, tp.count(a.tape), int(a.n), a.order);
     const CellMech cm{m.xd, m.xi, m.ceff, m.M, m.xtroe, m.xboth};
     const size_t lds = size_t(Sweep<K, EL>::kSize) * sizeof(double);
     hipLaunchKernelGGL((sweep_kernel<K, EL>), dim3(unsigned(a.n)), dim3(64), lds, s, cm, a);

@@ -149,3 +149,36 @@ def test_taped_step_order(h2_path, h2_mech, n):
     for a, b, c in zip(*out):
         assert np.array_equal(a, b)
         assert np.array_equal(a[..., ok], c[..., ok]) and np.all(c[..., ~ok] == 0)
+
+
+def test_sweep_without_room_for_the_order(h2_path, h2_mech):
+    """A workspace of the per-cell gradients alone (8 M n bytes, without the cell order) is accepted and gives the
+    same bits; one byte less is refused."""
+    import ctypes as C
+
+    import torch
+    import paper_2210_07094_amd as df
+    from paper_2210_07094_amd import _lib
+    from test_gpu_adjoint import _taped
+    gm, n = df.Mechanism(h2_path), 70
+    f = fields.ignition_cells(h2_mech, n=n, seed=4)
+    print("case: sweep with a workspace of 8 M n bytes", flush=True)
+    _, p, _, tape, _, _ = _taped(gm, f, dt=1e-7, cap=512)
+    gen = torch.Generator(device="cuda:0").manual_seed(2)
+    Tb = torch.randn(n, dtype=torch.float64, device="cuda:0", generator=gen)
+    Yb = torch.randn(9, n, dtype=torch.float64, device="cuda:0", generator=gen)
+    ref = gm.chem_adjoint(p, tape, 512, Tb, Yb)
+    M, L = gm.n_reactions, _lib.lib()
+    out = [torch.empty_like(x) for x in ref]
+    ws = torch.empty(8 * M * n, dtype=torch.uint8, device="cuda:0")
+
+    def call(size):
+        q = [C.c_void_p(x.data_ptr()) for x in (p, tape, Tb, Yb, *out, ws)]
+        return L.df_chem_adjoint(gm._h, n, n, q[0], q[1], tape.numel(), 512, q[2], q[3], q[4], q[5], q[6], q[7], q[8],
+                                 size, C.c_void_p(torch.cuda.current_stream().cuda_stream))
+
+    assert call(ws.numel() - 1) == _lib.DF_E_INVALID
+    assert call(ws.numel()) == _lib.DF_OK
+    torch.cuda.synchronize()
+    for a, b in zip(ref, out):
+        assert torch.equal(a, b)
