@@ -79,8 +79,8 @@ def integrator_lane_ops(mech):
 
 # HBM traffic of the integrator kernel, from rocprofv3 FETCH_SIZE / WRITE_SIZE runs of this
 # benchmark scaled by what the same counters read for the benchmark's plain copy kernels
-TRAFFIC_FILE = os.path.join(ROOT, "profiles", "chem_coop_head_kernel_field65536_traffic.txt")
-KERNEL_SOURCES = ["df_chem_coop.hip", "df_kinetics.h", "df_internal.h"]
+TRAFFIC_FILE = os.path.join(ROOT, "profiles", "chem_cell_kernel_field65536_traffic.txt")
+KERNEL_SOURCES = ["df_chem_cell.hip", "df_cell.h", "df_kinetics.h", "df_internal.h"]
 
 
 def kernel_sources_sha256():
@@ -244,7 +244,7 @@ def adjoint_study(gm, mech_h, dev, with_cpu, threads):
            "taped_step_ms": t_tape, "reverse_sweep_ms": t_sweep,
            "gradient_cells_per_s": n / ((t_tape + t_sweep) * 1e-3),
            "full_jacobian_cells_per_s": n / ((t_tape + (K + 1) * t_sweep) * 1e-3),
-           "roofline": {"bound": "alu", "kernel": "adjoint_kernel<9> (FP64 VALU, 8 lanes per cell)",
+           "roofline": {"bound": "alu", "kernel": "sweep_kernel<9, 6> (FP64 VALU, one wavefront per cell)",
                         "achieved": tflops, "peak": PEAK_FP64_TFLOPS, "unit": "TFLOP/s",
                         "frac": tflops / PEAK_FP64_TFLOPS, "traffic": None, "lane_ops": aops}}
     if with_cpu:
@@ -348,11 +348,11 @@ def large_mechanism_study(dev, with_cpu, threads, n=65536):
     ops = integrator_lane_ops(mech)
     tflops = 2.0 * ops["per_attempt"] * attempts / (ms * 1e-3) / 1e12
     out = {"workload": f"hydrocarbon field recipe, {n} cells, 53 species / 325 reactions (seeded), dt = 1 us, "
-                       "one wavefront per cell",
+                       "one block of eight wavefronts per cell",
            "n_cells": n, "ms": ms, "cells_per_s": n / (ms * 1e-3), "attempts": attempts,
            "attempts_per_s": attempts / (ms * 1e-3), "accepted_mean": float(nsn[:n].mean()),
            "accepted_max": int(nsn[:n].max()), "status_counts": np.bincount(st.cpu().numpy()).tolist(),
-           "roofline": {"bound": "alu", "kernel": "chem_wave_kernel<53> (FP64 VALU, one wavefront per cell)",
+           "roofline": {"bound": "alu", "kernel": "chem_block_kernel<53> (FP64 VALU, eight wavefronts per cell)",
                         "achieved": tflops, "peak": PEAK_FP64_TFLOPS, "unit": "TFLOP/s",
                         "frac": tflops / PEAK_FP64_TFLOPS, "lane_ops_per_attempt": ops}}
     # the DNN form at this size: a 55-3200-1600-800-53 BF16 network with seeded weights (no
@@ -780,7 +780,7 @@ def main():
                                "H2/air phi=1, 9 species/24 reactions (seeded), p=1 atm, dt=1e-6 s",
                    "n_cells": n, "dt": DT, "rtol": 1e-8, "mechanism": os.path.basename(MECH),
                    "dnn": os.path.basename(DNN_W), "snapshot": "0 (as generated)"},
-        "roofline": {"bound": "alu", "kernel": "chem_coop_head_kernel<9, 2> (FP64 VALU, 32 lanes per cell for the 512 hottest cells, 16 for the rest)",
+        "roofline": {"bound": "alu", "kernel": "chem_cell_kernel<9, 6, false> (FP64 VALU, one wavefront per cell)",
                      "achieved": chem_tflops,
                      "peak": PEAK_FP64_TFLOPS, "unit": "TFLOP/s", "frac": chem_tflops / PEAK_FP64_TFLOPS,
                      "traffic": measured_traffic(), "lane_ops_per_attempt": ops["per_attempt"],

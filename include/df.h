@@ -90,7 +90,8 @@ typedef struct {
                           where compiled, else one cell per lane, else as 3.  Where a
                           mechanism's rates fit the lanes of one wave (up to 31 reactions, four spare
                           lanes per falloff reaction), automatic, 2, 4 and 5 and the queue
-                          schedule all run one wavefront per cell with tables in registers.
+                          schedule (up to 360,448 cells; beyond, its 16-lane groups) all run one
+                          wavefront per cell with tables in registers.
                           Automatic, 2, 4 and 5 give the same bits */
     int32_t schedule;  /* 0 (default) or 1: static, one launch that gives each lane (or group of
                           16 lanes) one cell; 2: persistent work queue (needs the workspace):

@@ -311,6 +311,13 @@ __global__ __launch_bounds__(256) void tape_last_length(double *tape, int K, int
     tape[tp.h(cap - 1) + i] = dt - t;
 }
 
+// A queue call of so many cells that their total work sets the time and not the stiffest cell's chain: the
+// 16-lane queue, which takes the cold cells one per lane and four cells per wave otherwise, needs less work per
+// cell than one wave per cell, whose shorter chain no longer matters.  Mixing layer with local time steps, one
+// wave / 16 lanes: 262,144 cells 23.8 / 29.6 ms, 350,000 30.6 / 30.7, 450,000 36.7 / 33.5, 1,000,000 74.2 / 65.8.
+// (Static launches, whose 16-lane form waits for the slowest of four cells: 74.0 / 98.6 ms at 1,000,000.)
+bool work_bound_queue(const MechDev &m, int64_t n) { return n > 352 * 1024 && chem_queue_capacity(m) > 0; }
+
 // scalar dt (dts == nullptr) or per-cell dt
 df_status chem_step_impl(const char *who, const df_mech *mech, int64_t n_cells, int64_t ld, double dt,
                          const double *dts, const double *p, double *T, double *Y, double *h_inout, double *rr,
@@ -340,7 +347,8 @@ df_status chem_step_impl(const char *who, const df_mech *mech, int64_t n_cells, 
     const Work wk = workspace ? work_parts(workspace) : Work{nullptr, nullptr, nullptr, nullptr, nullptr};
     if (workspace) st = order_cells(a, wk, s);
     if (st == DF_OK) {
-        if (workspace && chem_cell_supported(mech->dev) && (o.schedule == 2 || (o.mapping != 1 && o.mapping != 3))) {
+        if (workspace && chem_cell_supported(mech->dev) &&
+            (o.schedule == 2 ? !work_bound_queue(mech->dev, n_cells) : (o.mapping != 1 && o.mapping != 3))) {
             st = launch_chem_cell(mech->dev, a, CellQueue{nullptr, nullptr, wk.idx, wk.groups, nullptr, 0}, s);
         } else if (o.schedule == 2) {
             const int32_t cap = chem_queue_capacity(mech->dev);
@@ -527,7 +535,7 @@ extern "C" df_status df_chem_autotune(const df_mech *mech, int64_t n_cells, int6
     auto *Yc = reinterpret_cast<double *>(base + order_bytes(n_cells) + al256(size_t(n_cells) * 8));
     // with one wave per cell every queue schedule and the 16- and 32-lane mappings are the same launch
     const bool cell = chem_cell_supported(mech->dev);
-    const int32_t cap = cell ? 0 : chem_queue_capacity(mech->dev);
+    const int32_t cap = (cell && !work_bound_queue(mech->dev, n_cells)) ? 0 : chem_queue_capacity(mech->dev);
     struct Cand {
         int32_t schedule, coop_blocks, mapping;
     };

@@ -1,7 +1,7 @@
 """GPU checks of the one-wave-per-cell kernel for small mechanisms at the edges of its layout: how many
 reactions and falloff reactions fit the lanes (and the first sizes that do not, which take the 16-lane
 kernel), a species on both sides of a reaction, and the cell counts at which the queue's groups, fixed
-first units and four-cell units begin and end.
+first units and four-cell units begin and end, and at which a queue call leaves the kernel.
 
 Parity bar as in test_gpu_chem (<= 1e-8 relative against the oracle where the accept/reject sequences
 agree); a cell's result does not depend on who takes it, so the queue (with workspace) and the plain
@@ -182,3 +182,33 @@ def test_sweep_without_room_for_the_order(h2_path, h2_mech):
     torch.cuda.synchronize()
     for a, b in zip(ref, out):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("n", [352 * 1024, 352 * 1024 + 1])
+def test_queue_of_many_cells(h2_path, h2_mech, n):
+    """Where a queue call changes from one wave per cell (the bits of the static launch) to the 16-lane queue (the
+    parity bar against it)."""
+    import torch
+    import paper_2210_07094_amd as df
+    gm = df.Mechanism(h2_path)
+    f = fields.ignition_cells(h2_mech, n=1001, seed=3)
+    f = {"T": np.resize(f["T"], n), "p": np.resize(f["p"], n),
+         "Y": np.ascontiguousarray(f["Y"][:, np.arange(n) % 1001])}
+    print(f"case: queue, {n} cells", flush=True)
+    a = _step(gm, f, 1e-8, True)
+    t = {k: torch.tensor(f[k], device="cuda:0") for k in ("T", "p", "Y")}
+    st = torch.full((n,), -7, dtype=torch.int32, device="cuda:0")
+    ns = torch.full((2 * n,), -7, dtype=torch.int32, device="cuda:0")
+    gm.chem_step(t["T"], t["p"], t["Y"], 1e-8, status=st, n_steps=ns, workspace=gm.workspace(n),
+                 opts=df.chem_opts(schedule=2))
+    torch.cuda.synchronize()
+    b = {"T": t["T"].cpu().numpy(), "Y": t["Y"].cpu().numpy(), "status": st.cpu().numpy(),
+         "n_acc": ns[:n].cpu().numpy(), "n_rej": ns[n:].cpu().numpy()}
+    np.testing.assert_array_equal(a["status"], b["status"])
+    if n <= 352 * 1024:
+        for k in ("T", "Y", "n_acc", "n_rej"):
+            np.testing.assert_array_equal(a[k], b[k])
+    else:
+        worst, flipped, tol_err = compare(b, a)
+        assert worst <= 1e-8, worst
+        assert flipped <= n // 500 and tol_err <= 10.0, (flipped, tol_err)
