@@ -135,7 +135,8 @@ struct Coef {
 };
 
 // e^x: n = rint(x / ln 2), r = x - n ln 2 in two parts, e^r = 1 + (r + r^2 P(r)), scaled by 2^n.
-// Overflow gives +inf, underflow 0 or a denormal, NaN stays NaN.
+// Overflow gives +inf, underflow 0 or a denormal, NaN stays NaN.  |x| below 1e44: beyond, the rounding of n ln 2 leaves
+// an r whose polynomial overflows (the coefficient rows are kept at 1e30 when they are packed).
 __device__ __forceinline__ double dexp(const Coef &c, double x) {
     const double n = __builtin_rint(x * c.log2e);
     const double r = fma(n, c.ln2l, fma(n, c.ln2h, x));

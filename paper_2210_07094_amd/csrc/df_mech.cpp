@@ -199,6 +199,11 @@ static void pack_tables(const HostMech &m, const std::vector<int> &order, std::v
     }
 }
 
+// A factor of T, 1/T or ln T inside an exponential, at most 1e30 in magnitude: a larger one (T*** = 1e-100 switches a
+// Troe term off as well as 1e-30 does) gives the same 0, 1 or infinity at any temperature, but the kernels' own
+// exponential (dexp of df_cell.h) does not hold for arguments beyond some 1e44.
+static double exponent_term(double x) { return std::min(std::max(x, -1e30), 1e30); }
+
 // Tables of the cooperative kernel (layout in df_internal.h).  The equilibrium constant
 // and the reaction enthalpy are linear in the NASA-7 coefficients, so each reaction gets
 // its own coefficient rows over a few functions of T: with
@@ -282,6 +287,7 @@ static void pack_coop_tables(const HostMech &m, const std::vector<int> &order, C
             cr[21] = -1.0 / m.troe[4 * j + 2];
             cr[22] = -m.troe[4 * j + 3];
         }
+        for (int i : {1, 2, 4, 5, 17, 18, 20, 21, 22}) cr[i] = exponent_term(cr[i]);
         cr[23] = nr;
         cr[24] = np;
         if (m.type[j] != 0)
