@@ -41,6 +41,7 @@ struct SweepArgs {
     const double *ad;   // slot lists
     const int *ai;
     int32_t *order;  // cells, most sub-steps first; null: by index
+    int64_t first;   // the launch's first place in that order
 };
 
 // The cells by decreasing number of sub-steps (the sweep's chains; a late start of a long one would set
@@ -414,7 +415,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1))) void
     constexpr int N = C::N, NI = C::NI;
     extern __shared__ double sh[];
     const int lane = threadIdx.x, r = lane & 15, g = lane >> 4;
-    const int64_t i = a.order ? int64_t(a.order[blockIdx.x]) : int64_t(blockIdx.x);
+    const int64_t slot = a.first + blockIdx.x, i = a.order ? int64_t(a.order[slot]) : slot;
     for (int e = lane; e < S::kSize; e += 64) sh[e] = 0.0;
     lds_order();
     for (int e = lane; e < 32 * K; e += 64) {
@@ -520,15 +521,18 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1))) void
 }
 
 template <int K, int EL>
-df_status launch_k(const MechDev &m, const SweepArgs &a, hipStream_t s) {
+df_status launch_k(const MechDev &m, SweepArgs a, hipStream_t s) {
     const Tape tp(K, a.n, a.cap);
     if (a.order)
         hipLaunchKernelGGL(sweep_order, dim3(1), dim3(kSortThreads), 0, s, tp.count(a.tape), int(a.n), a.order);
     const CellMech cm{m.xd, m.xi, m.ceff, m.M, m.xtroe, m.xboth};
     const size_t lds = size_t(Sweep<K, EL>::kSize) * sizeof(double);
-    hipLaunchKernelGGL((sweep_kernel<K, EL>), dim3(unsigned(a.n)), dim3(64), lds, s, cm, a);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return fail(DF_E_HIP, std::string("df_chem_adjoint launch: ") + hipGetErrorString(e));
+    for (; a.first < a.n; a.first += max_blocks(64)) {
+        const int64_t blocks = a.n - a.first < max_blocks(64) ? a.n - a.first : max_blocks(64);
+        hipLaunchKernelGGL((sweep_kernel<K, EL>), dim3(unsigned(blocks)), dim3(64), lds, s, cm, a);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return fail(DF_E_HIP, std::string("df_chem_adjoint launch: ") + hipGetErrorString(e));
+    }
     return DF_OK;
 }
 
@@ -540,7 +544,7 @@ bool sweep_cell_supported(const MechDev &m) { return m.xel == 6 && m.xad; }
 df_status launch_sweep_cell(const MechDev &m, int64_t n, int64_t ld, const double *p, const double *tape, int32_t cap,
                             const double *Tb, const double *Yb, double *T0b, double *Y0b, double *thc, double *wth,
                             int32_t *order, hipStream_t s) {
-    const SweepArgs a{n, ld, p, tape, cap, Tb, Yb, T0b, Y0b, thc, wth, m.src, m.sp, m.xad, m.xai, order};
+    const SweepArgs a{n, ld, p, tape, cap, Tb, Yb, T0b, Y0b, thc, wth, m.src, m.sp, m.xad, m.xai, order, 0};
 #define DF_CASE(k)                                   \
     case k:                                          \
         return launch_k<k, 6>(m, a, s);

@@ -668,7 +668,6 @@ bool chem_block_supported(const MechDev &m) {
 df_status launch_chem_block(const MechDev &m, const StepArgs &a, const int32_t *cidx, const int32_t *dcount,
                             hipStream_t stream) {
     if (a.n == 0) return DF_OK;
-    if (a.n > 0x7fffffff) return fail(DF_E_UNSUPPORTED, "df_chem_step: too many cells for one launch");
     if (a.tape) return fail(DF_E_UNSUPPORTED, "df_chem_step: the one-block-per-cell kernel records no tape");
     const size_t lds = Block<53>::lds_bytes(m);
     auto kernel = chem_block_kernel<53>;
@@ -678,7 +677,7 @@ df_status launch_chem_block(const MechDev &m, const StepArgs &a, const int32_t *
         return fail(DF_E_HIP, "df_chem_step: cannot raise the LDS limit of the one-block-per-cell kernel");
     // a device-side count (the fallback cells of a DNN step, usually few): an empty list then costs at most
     // 2,048 blocks instead of one per cell
-    const int64_t blocks = dcount ? std::min<int64_t>(a.n, 2048) : a.n;
+    const int64_t blocks = std::min(a.n, dcount ? 2048 : max_blocks(kBT));
     hipLaunchKernelGGL(kernel, dim3(unsigned(blocks)), dim3(kBT), lds, stream, m, a, cidx, dcount);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(DF_E_HIP, std::string("chem_step block launch: ") + hipGetErrorString(e));

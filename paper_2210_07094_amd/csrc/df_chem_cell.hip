@@ -365,7 +365,7 @@ df_status launch_k(const MechDev &m, const StepArgs &a, const CellQueue &q, hipS
     } else if (q.dcount) {
         blocks = blocks < int64_t(cus) * 8 ? blocks : int64_t(cus) * 8;
     }
-    if (blocks > 0x7fffffff) return fail(DF_E_UNSUPPORTED, "chem_step: too many cells for one launch");
+    blocks = blocks < max_blocks(64) ? blocks : max_blocks(64);  // (beyond, the blocks stride)
     const size_t lds = size_t(waves) * CellWave<K, EL>::kEnd * sizeof(double);
     const CellMech cm{m.xd, m.xi, m.ceff, m.M, m.xtroe, m.xboth};
     if (a.tape)

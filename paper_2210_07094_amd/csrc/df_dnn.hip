@@ -58,7 +58,7 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 constexpr int kPreCells = 32;
 
 template <int K>
-__global__ __launch_bounds__(kPreThreads) void pre_kernel(DnnDevParams prm, int64_t n, int64_t n_pad, int64_t ld,
+__global__ __launch_bounds__(kPreThreads) void pre_kernel(DnnDevParams prm, int64_t first, int64_t n, int64_t n_pad, int64_t ld,
                                                           const double *__restrict__ p, const double *__restrict__ T,
                                                           const double *__restrict__ Y, bf16_t *__restrict__ xb,
                                                           int in_pad, int8_t *__restrict__ flag,
@@ -69,8 +69,8 @@ __global__ __launch_bounds__(kPreThreads) void pre_kernel(DnnDevParams prm, int6
     __shared__ __attribute__((aligned(16))) bf16_t xs[kPreCells * LDX];
     __shared__ int bad[kPreCells];  // bit 0: out of range, bit 1: not finite
     const int t = threadIdx.x, c = t % kPreCells, f0 = t / kPreCells;
-    const int64_t i0 = int64_t(blockIdx.x) * kPreCells, i = i0 + c;
-    if (blockIdx.x == 0 && t == 0) *count = 0;
+    const int64_t i0 = first + int64_t(blockIdx.x) * kPreCells, i = i0 + c;
+    if (i0 == 0 && t == 0) *count = 0;
     if (t < kPreCells) bad[t] = 0;
     for (int e = t; e < kPreCells * LDX / 8; e += kPreThreads)
         reinterpret_cast<u32x4 *>(xs)[e] = u32x4{0u, 0u, 0u, 0u};
@@ -144,7 +144,7 @@ __device__ __forceinline__ double row_add(double x) {
 }
 
 template <int K>
-__global__ __launch_bounds__(kPostThreads) void post_kernel(DnnDevParams prm, MechDev m, int64_t n, int64_t ld,
+__global__ __launch_bounds__(kPostThreads) void post_kernel(DnnDevParams prm, MechDev m, int64_t first, int64_t n, int64_t ld,
                                                             double dt, const bf16_t *__restrict__ h, int h_ld,
                                                             const bf16_t *__restrict__ W, const float *__restrict__ b,
                                                             int k_in, const int8_t *__restrict__ flag,
@@ -162,7 +162,7 @@ __global__ __launch_bounds__(kPostThreads) void post_kernel(DnnDevParams prm, Me
     __shared__ double s0[kPostCells * NP], s1[kPostCells * NP];
     const int lane = int(threadIdx.x) & 63, wv = int(threadIdx.x) >> 6;
     const int fr = lane & 15, fg = lane >> 4;
-    const int64_t cell0 = int64_t(blockIdx.x) * kPostCells;
+    const int64_t cell0 = first + int64_t(blockIdx.x) * kPostCells;
     if (kSplit || wv < NT) {
         floatx4 acc = {0.f, 0.f, 0.f, 0.f};
         const bf16x8 zero = {};
@@ -377,6 +377,12 @@ uint8_t e4m3_byte(float v) {
     return uint8_t(sgn | ((E + 7) << 3) | (m - 8));
 }
 
+// The input and output kernels take up to 16 threads per cell, and a launch holds fewer than 2^32: cells from `first`
+// on in launches of at most kLaunchCells.
+constexpr int64_t kLaunchCells = int64_t(1) << 27;
+static_assert(kPostThreads / kPostCells <= 16 && kPreThreads / kPreCells <= 16, "threads per cell");
+int64_t launch_cells(int64_t first, int64_t n) { return std::min(kLaunchCells, n - first); }
+
 template <int K>
 df_status launch_dnn_k(const df_dnn *d, const df_mech *m, int64_t n, int64_t ld, double dt, const double *p,
                        double *T, double *Y, double *rr, int32_t *status, void *ws, const df_dnn_opts &o,
@@ -390,8 +396,10 @@ df_status launch_dnn_k(const df_dnn *d, const df_mech *m, int64_t n, int64_t ld,
     auto *idx = reinterpret_cast<int32_t *>(base + w.o_idx);
     auto *cnt = reinterpret_cast<int32_t *>(base + w.o_cnt);
     const int in_pad = d->layers[0].k_pad;
-    hipLaunchKernelGGL(pre_kernel<K>, dim3(unsigned((w.n_pad + kPreCells - 1) / kPreCells)), dim3(kPreThreads), 0,
-                       s, d->prm, n, w.n_pad, ld, p, T, Y, xb, in_pad, flag, cnt, status, rr, o.fallback);
+    for (int64_t first = 0; first < w.n_pad; first += kLaunchCells)
+        hipLaunchKernelGGL(pre_kernel<K>, dim3(unsigned((launch_cells(first, w.n_pad) + kPreCells - 1) / kPreCells)),
+                           dim3(kPreThreads), 0, s, d->prm, first, n, w.n_pad, ld, p, T, Y, xb, in_pad, flag, cnt, status,
+                           rr, o.fallback);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(DF_E_HIP, std::string("dnn pre launch: ") + hipGetErrorString(e));
     // hidden layers
@@ -440,9 +448,10 @@ df_status launch_dnn_k(const df_dnn *d, const df_mech *m, int64_t n, int64_t ld,
         in_ld = out_ld;
     }
     const DnnLayer &Lo = d->layers.back();
-    hipLaunchKernelGGL(post_kernel<K>, dim3(unsigned((n + kPostCells - 1) / kPostCells)), dim3(kPostThreads), 0, s,
-                       d->prm, m->dev, n, ld, dt, in, in_ld, Lo.W, Lo.b, Lo.k_pad, flag, p, T, Y, rr, status,
-                       o.renormalise, idx, cnt, o.fallback);
+    for (int64_t first = 0; first < n; first += kLaunchCells)
+        hipLaunchKernelGGL(post_kernel<K>, dim3(unsigned((launch_cells(first, n) + kPostCells - 1) / kPostCells)),
+                           dim3(kPostThreads), 0, s, d->prm, m->dev, first, n, ld, dt, in, in_ld, Lo.W, Lo.b, Lo.k_pad,
+                           flag, p, T, Y, rr, status, o.renormalise, idx, cnt, o.fallback);
     e = hipGetLastError();
     if (e != hipSuccess) return fail(DF_E_HIP, std::string("dnn post launch: ") + hipGetErrorString(e));
     if (o.fallback) {

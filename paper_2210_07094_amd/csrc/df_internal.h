@@ -213,6 +213,9 @@ df_status launch_chem_coop(const MechDev &m, const StepArgs &a, const CellQueue 
 // from the order, else slot s < *dcount (or n) takes cell cidx[s] (or s); writes the tape when given
 // its queue's counters: kCellQueues of them, 128 bytes apart, zero at the launch
 constexpr int kCellQueues = 8;
+// A launch holds fewer than 2^32 threads.  Kernels with one wave or block per cell start at most this many of
+// `threads` threads and stride over the rest.
+constexpr int64_t max_blocks(int threads) { return 0xffffffffll / threads; }
 bool chem_cell_supported(const MechDev &m);
 df_status launch_chem_cell(const MechDev &m, const StepArgs &a, const CellQueue &q, hipStream_t stream);
 // the taped step on it (df_chem.hip), in cost order where that pays

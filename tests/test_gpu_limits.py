@@ -1,12 +1,12 @@
 """GPU checks of the chemistry step at the far ends of what it accepts: exponents far outside the range of the
-exponential.
+exponential, and more cells than one launch has threads for.
 """
 import numpy as np
 import pytest
 
 import oracle
 import synth
-from synth import fields
+from synth import fields, testmechs
 from synth.mechfile import write_mech
 from test_gpu_chem import _gpu_step, compare
 from test_gpu_wave import HC_MECH
@@ -85,3 +85,100 @@ def test_far_out_exponents_adjoint(h2_path, tmp_path):
     for a, b in zip(*out):
         assert np.all(np.isfinite(a))
         np.testing.assert_allclose(a, b, rtol=1e-12, atol=1e-14 * np.abs(b).max())
+
+
+def _sparse_field(mech, n, at, K):
+    """n cells on the device, unusable (NaN) except for those in `at`, and the same few cells alone."""
+    import torch
+    few = {"T": np.full(at.size, 1100.0), "p": np.full(at.size, 101325.0), "Y": np.zeros((K, at.size))}
+    few["Y"][0], few["Y"][1] = 0.25, 0.75
+    f = {"T": torch.full((n,), float("nan"), dtype=torch.float64, device="cuda:0"),
+         "p": torch.full((n,), 101325.0, dtype=torch.float64, device="cuda:0"),
+         "Y": torch.zeros(K, n, dtype=torch.float64, device="cuda:0")}
+    f["T"][torch.as_tensor(at, device="cuda:0")] = 1100.0
+    f["Y"][0], f["Y"][1] = 0.25, 0.75
+    return few, f
+
+
+@pytest.mark.parametrize("path, K, n, workspace", [
+    ("iso", 2, 2**32 // 64, False),      # one wave per cell
+    ("iso", 2, 2**32 // 64 + 1, False),
+    ("iso", 2, 2**32 // 64 + 1, True),
+    ("hc", 53, 2**32 // 512, False),     # eight waves per cell
+    ("hc", 53, 2**32 // 512 + 1, False),
+])
+def test_more_cells_than_threads_of_a_launch(tmp_path, path, K, n, workspace):
+    import torch
+    import paper_2210_07094_amd as df
+    if path == "iso":
+        m, path = testmechs.isomerisation(kf=2e5), str(tmp_path / "iso.mech")
+        write_mech(path, m)
+    else:
+        m, path = synth.read_mech(HC_MECH), HC_MECH
+    gm = df.Mechanism(path)
+    at = np.array([0, 1, n // 2, n - 2, n - 1])
+    few, f = _sparse_field(m, n, at, K)
+    print(f"case: {n} cells, {K} species, workspace {workspace}", flush=True)
+    st = torch.full((n,), -7, dtype=torch.int32, device="cuda:0")
+    gm.chem_step(f["T"], f["p"], f["Y"], 1e-8, status=st, workspace=gm.workspace(n) if workspace else None)
+    torch.cuda.synchronize()
+    assert torch.equal(st.bincount().cpu(), torch.tensor([at.size, *[0] * (df.CELL_NONFINITE - 1), n - at.size]))
+    ref = _gpu_step(gm, few, 1e-8)
+    np.testing.assert_array_equal(f["T"][torch.as_tensor(at, device="cuda:0")].cpu().numpy(), ref["T"])
+    np.testing.assert_array_equal(f["Y"][:, torch.as_tensor(at, device="cuda:0")].cpu().numpy(), ref["Y"])
+
+
+def test_adjoint_of_more_cells_than_threads_of_a_launch(tmp_path):
+    import torch
+    import paper_2210_07094_amd as df
+    m, path, n = testmechs.isomerisation(kf=2e5), str(tmp_path / "iso.mech"), 2**32 // 64 + 1
+    write_mech(path, m)
+    gm = df.Mechanism(path)
+    at = np.array([0, 1, n // 2, n - 2, n - 1])
+    few, f = _sparse_field(m, n, at, 2)
+    at_d = torch.as_tensor(at, device="cuda:0")
+    out = []
+    for T, p, Y in ((f["T"], f["p"], f["Y"]),
+                    [torch.tensor(few[k], dtype=torch.float64, device="cuda:0") for k in ("T", "p", "Y")]):
+        print(f"case: adjoint of {T.numel()} cells", flush=True)
+        tape = gm.chem_step_taped(T, p, Y, 1e-9, max_substeps=4)
+        Tb, Yb = torch.ones_like(T), torch.ones_like(Y)
+        Yb[1] = 0.25
+        out.append(gm.chem_adjoint(p, tape, 4, Tb, Yb))
+        torch.cuda.synchronize()
+    (T0, Y0, lnA, s), (rT0, rY0, rlnA, rs) = out
+    assert bool((rY0 != 0).any())
+    for a, b in ((T0, rT0), (Y0, rY0), (lnA, rlnA)):
+        assert torch.equal(a[..., at_d], b)
+        assert int((a != 0).sum()) == int((b != 0).sum())
+    torch.testing.assert_close(s, rs, rtol=1e-13, atol=0.0)
+
+
+def test_network_on_more_cells_than_threads_of_a_launch(tmp_path):
+    """16 threads per cell in the output kernel; the network is the smallest there is (2 species, 160 wide)."""
+    import torch
+    import paper_2210_07094_amd as df
+    from test_gpu_dnn import _net
+    m, path, n = testmechs.isomerisation(kf=2e5), str(tmp_path / "iso.mech"), 2**32 // 16 + 1
+    write_mech(path, m)
+    _net(tmp_path / "n.dfdnn", K=2, hidden=(160,))
+    gm = df.Mechanism(path)
+    dnn = df.DNN(tmp_path / "n.dfdnn", gm)
+    torch.cuda.empty_cache()
+    if torch.cuda.mem_get_info()[0] < dnn.workspace_bytes(n) + 48 * n:
+        pytest.skip("not enough device memory for that many cells")
+    at = np.array([0, 1, n // 2, n - 2, n - 1])
+    few, f = _sparse_field(m, n, at, 2)
+    print(f"case: network on {n} cells", flush=True)
+    st = torch.full((n,), -7, dtype=torch.int32, device="cuda:0")
+    ws = dnn.workspace(n)
+    dnn.step(f["T"], f["p"], f["Y"], 1e-6, status=st, workspace=ws, opts=df.dnn_opts(fallback=0))
+    torch.cuda.synchronize()
+    del ws
+    assert torch.equal(st.bincount().cpu(), torch.tensor([at.size, *[0] * (df.CELL_NONFINITE - 1), n - at.size]))
+    r = [torch.tensor(few[k], dtype=torch.float64, device="cuda:0") for k in ("T", "p", "Y")]
+    dnn.step(r[0], r[1], r[2], 1e-6, opts=df.dnn_opts(fallback=0))
+    at_d = torch.as_tensor(at, device="cuda:0")
+    assert torch.equal(f["T"][at_d], r[0]) and torch.equal(f["Y"][:, at_d], r[2])
+    del f, st
+    torch.cuda.empty_cache()
