@@ -27,14 +27,12 @@ FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", "-I", os.path.j
 
 SOURCES = ["df_mech.cpp", "df_chem.hip", "df_chem_cv.hip", "df_chem_wave.hip", "df_chem_block.hip", "df_chem_coop.hip", "df_chem_cell.hip", "df_dnn.hip", "df_mlp.hip", "df_adjoint.hip", "df_adjoint_cell.hip", "df_train.hip", "df_rollout.hip", "df_stats.hip"]
 
-# per-source additions: the constant-volume kernel is built with the machine instruction
-# scheduler off and the one-wavefront-per-cell kernel with the scheduler's max-memory-clause
-# strategy.  -O2 and -O3 builds with the default scheduling gave wrong results on gfx950, while
-# these builds, -O1 and the CPU build of the same sources under sanitizers (tests/test_cpu_emu.py)
-# agree with the oracle; the optimised IR of both files carries no undefined value into the
-# arithmetic, so the difference arises in code generation.  Their parity tests check these builds.
-EXTRA = {"df_chem_cv.hip": ["-mllvm", "-enable-misched=0"],
-         "df_chem_wave.hip": ["-mllvm", "-amdgpu-sched-strategy=max-memory-clause"]}
+# per-source additions: the one-wavefront-per-cell kernel is built with the scheduler's max-memory-clause
+# strategy.  Builds of it with the default scheduling gave wrong results on gfx950, while this build, -O1
+# and the CPU build of the same source under sanitizers (tests/test_cpu_emu.py) agree with the
+# oracle; the optimised IR carries no undefined value into the arithmetic, so the difference arises in
+# code generation.  Its parity tests check this build.
+EXTRA = {"df_chem_wave.hip": ["-mllvm", "-amdgpu-sched-strategy=max-memory-clause"]}
 
 
 def _compile(src: str, verbose: bool) -> str:

@@ -31,10 +31,16 @@ __global__ __launch_bounds__(kWave) void chem_step_kernel(MechDev m, StepArgs a,
     C::init_lds(sh);
     const int64_t slot = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     const int64_t limit = dcount ? int64_t(*dcount) : a.n;
-    if (slot >= limit) return;
     LaneTask<K> c;
-    bool have = lane_load<K>(a, cidx ? int64_t(cidx[slot]) : slot, c);
-    while (have) have = !lane_attempt<K>(m, a, sh, c);
+    lane_idle<K>(c);
+    bool have = slot < limit && lane_load<K>(a, cidx ? int64_t(cidx[slot]) : slot, c);
+    while (__ballot(have) != 0ull) {
+        const int st = lane_attempt<K>(m, a, sh, c);
+        if (have && st >= 0) {
+            lane_finish<K>(m, a, c, st);
+            have = false;
+        }
+    }
 }
 
 }  // namespace

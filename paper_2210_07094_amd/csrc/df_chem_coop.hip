@@ -789,9 +789,15 @@ __global__ __launch_bounds__(64) void chem_queue_kernel(MechDev mg, StepArgs a, 
                 if (lane_load<K>(a, i, c)) return true;
             }
         };
+        lane_idle<K>(c);
         bool have = next();
-        while (have)
-            if (lane_attempt<K>(mg, a, sh, c)) have = next();
+        while (__ballot(have) != 0ull) {
+            const int st = lane_attempt<K>(mg, a, sh, c);
+            if (have && st >= 0) {
+                lane_finish<K>(mg, a, c, st);
+                have = next();
+            }
+        }
         __syncthreads();  // the per-lane arrays are dead before the tables overwrite them
     }
     const int r = lane & (G - 1);

@@ -6,15 +6,6 @@
 // the state (p = rho R T / Wbar).  The per-lane RODAS4 solver is the constant-pressure one with
 // its constant-volume thermodynamics (Cell<K, true>); species counts without a per-lane kernel
 // go to the one-wavefront-per-cell kernel's constant-volume instantiation (df_chem_wave.hip).
-//
-// This file is compiled on its own, with the machine instruction scheduler off: optimised
-// builds of this instantiation with the scheduler on produced wrong sub-steps on gfx950
-// (every attempt after the first rejected, the step length driven to 1e-17 s) while the same
-// source built without optimisation, built with FP contraction off, or run on the CPU under
-// sanitizers (tests/test_cpu_emu.py) gave the oracle's sub-step sequence; the constant-pressure
-// instantiation of the same solver is correct with the scheduler on, and the optimised IR of
-// this file carries no undefined value into the arithmetic.  The parity tests of the
-// constant-volume step check this build.
 #include <cmath>
 
 #include "df_internal.h"
@@ -36,10 +27,16 @@ __global__ __launch_bounds__(kWave) void chem_step_cv_kernel(MechDev m, StepArgs
     double *sh = lds + threadIdx.x;
     C::init_lds(sh);
     const int64_t slot = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (slot >= a.n) return;
     LaneTask<K> c;
-    bool have = lane_load<K>(a, slot, c);
-    while (have) have = !lane_attempt<K, true>(m, a, sh, c);
+    lane_idle<K>(c);
+    bool have = slot < a.n && lane_load<K>(a, slot, c);
+    while (__ballot(have) != 0ull) {
+        const int st = lane_attempt<K, true>(m, a, sh, c);
+        if (have && st >= 0) {
+            lane_finish<K>(m, a, c, st);
+            have = false;
+        }
+    }
 }
 
 template <int K>

@@ -400,6 +400,20 @@ __device__ bool lane_load(const StepArgs &a, int64_t i, LaneTask<K> &c) {
     return true;
 }
 
+// what a lane without a cell runs: a state at rest
+template <int K>
+__device__ __forceinline__ void lane_idle(LaneTask<K> &c) {
+    c.i = 0;
+    c.p = 101325.0;  // (as a density: some state, finite)
+    c.dtc = 1.0;
+#pragma unroll
+    for (int k = 0; k <= K; ++k) c.y[k] = k == 0 ? 300.0 : 1.0 / K;
+    c.h = 1.0;
+    c.t = c.h_final = 0.0;
+    c.acc = c.rej = 0;
+    c.prev_rej = c.fresh = false;
+}
+
 // write the results of the lane's cell
 template <int K>
 __device__ void lane_finish(const MechDev &m, const StepArgs &a, const LaneTask<K> &c, int st) {
@@ -429,22 +443,24 @@ __device__ void lane_finish(const MechDev &m, const StepArgs &a, const LaneTask<
     }
 }
 
-// One RODAS4 attempt of the lane's cell (the first attempt of a cell without a step
-// hint also picks the initial step from f(y0)).  Returns true when the cell is done and
-// its results have been written.
+// One RODAS4 attempt of the lane's cell (the first attempt of a cell without a step hint also picks the initial step
+// from f(y0)).  Returns -1 while the cell goes on, else its end status; lane_finish then writes the results.
+//
+// Every lane of the wave runs the attempt, also one without a cell (its numbers go nowhere).  The attempt needs more
+// registers than there are, and where lanes left the wave around it the built code lost values of those that
+// went on: of a queue of cold cells, the ones whose neighbours finished first ended at the sub-step limit (16 of 400,000
+// mixing-layer cells, all with four falloff reactions), at -O2 and -O3 under three schedulers and not at -O1.  Now the
+// only code in which lanes part is the few instructions that end a cell, and every scheduling agrees with the oracle.
 template <int K, bool CV = false>
-__device__ bool lane_attempt(const MechDev &m, const StepArgs &a, double *sh, LaneTask<K> &c) {
+__device__ __forceinline__ int lane_attempt(const MechDev &m, const StepArgs &a, double *sh, LaneTask<K> &c) {
     using C = Cell<K, CV>;
     constexpr int N = K + 1;
     const Opts &o = a.o;
-    if (c.acc + c.rej >= o.max_steps) {
-        lane_finish<K>(m, a, c, DF_CELL_MAX_STEPS);
-        return true;
-    }
+    const bool spent = c.acc + c.rej >= o.max_steps;
     double W[N][N], f0[N];
     int piv[N];
     C::jacobian(m, c.p, c.y, sh, W, f0);
-    if (c.fresh) {
+    if (__ballot(c.fresh) != 0ull) {
         // initial sub-step from the weighted norms of y0 and f(y0)
         double ny = 0.0, nf = 0.0;
 #pragma unroll
@@ -455,8 +471,9 @@ __device__ bool lane_attempt(const MechDev &m, const StepArgs &a, double *sh, La
         }
         ny = sqrt(ny / N);
         nf = sqrt(nf / N);
-        c.h = (nf > 0.0) ? fmin(0.01 * ny / nf, c.dtc) : c.dtc;
-        if (!(c.h >= o.h_min)) c.h = o.h_min;
+        double h0 = (nf > 0.0) ? fmin(0.01 * ny / nf, c.dtc) : c.dtc;
+        h0 = (h0 >= o.h_min) ? h0 : o.h_min;
+        c.h = (c.fresh && !spent) ? h0 : c.h;
         c.fresh = false;
     }
     const bool last = (c.t + c.h >= c.dtc);
@@ -533,28 +550,19 @@ __device__ bool lane_attempt(const MechDev &m, const StepArgs &a, double *sh, La
     else
         fac = fmin(fmx, fmax(0.2, 0.9 * pow(err, -0.25)));
 
-    if (isfinite(err) && err <= 1.0) {
-        ++c.acc;
+    const bool accept = isfinite(err) && err <= 1.0 && !spent;
+    const bool reject = !accept && !spent;
+    c.acc += accept;
+    c.rej += reject;
 #pragma unroll
-        for (int k = 0; k < N; ++k) c.y[k] = yn[k];
-        c.h_final = c.h;
-        c.prev_rej = false;
-        if (last) {
-            lane_finish<K>(m, a, c, DF_CELL_OK);
-            return true;
-        }
-        c.t += ht;
-        c.h = ht * fac;
-    } else {
-        ++c.rej;
-        c.prev_rej = true;
-        c.h = ht * fac;
-        if (c.h < o.h_min) {
-            lane_finish<K>(m, a, c, DF_CELL_H_UNDERFLOW);
-            return true;
-        }
-    }
-    return false;
+    for (int k = 0; k < N; ++k) c.y[k] = accept ? yn[k] : c.y[k];
+    c.h_final = accept ? c.h : c.h_final;
+    c.prev_rej = spent ? c.prev_rej : reject;
+    int st = spent ? DF_CELL_MAX_STEPS : (accept && last) ? DF_CELL_OK : -1;
+    c.t = (accept && !last) ? c.t + ht : c.t;
+    c.h = (spent || (accept && last)) ? c.h : ht * fac;
+    if (reject && c.h < o.h_min) st = DF_CELL_H_UNDERFLOW;
+    return st;
 }
 
 }  // namespace
