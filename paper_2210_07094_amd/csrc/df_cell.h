@@ -252,6 +252,23 @@ struct CellWave {
         for (int i = 0; i < EL; ++i) o.li[i] = I();
     }
 
+    // the LDS of a wave at its start: zeros, and the efficiencies of the reactions
+    __device__ __forceinline__ static void load_eff(const CellMech &m, int lane, double *sh) {
+        constexpr int kPer = (32 * K + 63) / 64;
+        double ef[kPer];
+#pragma unroll
+        for (int e = 0; e < kPer; ++e) {
+            const int i = 64 * e + lane, j = i / K;
+            ef[e] = (j < m.M) ? m.eff[j * (K + 4) + i % K] : 0.0;
+        }
+#pragma unroll
+        for (int e = 0; e < (oEff + 63) / 64; ++e)
+            if (64 * e + lane < oEff) sh[64 * e + lane] = 0.0;
+#pragma unroll
+        for (int e = 0; e < kPer; ++e)
+            if (64 * e + lane < 32 * K) sh[oEff + 64 * e + lane] = ef[e];
+    }
+
     // what the rates share with the caller
     struct Rates {
         double T, iT, Wbar, irho, c6, Mc, kk, c0, c1, c2, P, X, dl, gM, cpR;
@@ -328,9 +345,16 @@ struct CellWave {
             const double cc = fma(-0.67, lFc, -0.4);
             const double nn = fma(-1.27, lFc, 0.75);
             const double x = lPr + cc;
-            const double iden = frcp3(fma(-0.14, x, nn));
-            const double f1 = x * iden;
-            const double q1 = frcp3(fma(f1, f1, 1.0));
+            const double den = fma(-0.14, x, nn);
+            double iden, f1, q1;  // f1 = x/den, q1 = 1/(1 + f1^2)
+            if (JAC) {
+                iden = frcp3(den);
+                f1 = x * iden;
+                q1 = frcp3(fma(f1, f1, 1.0));
+            } else {
+                const double d2 = den * den;
+                q1 = d2 * frcp3(fma(x, x, d2));
+            }
             const double F = dexp(kc, kLn10 * (lFc * q1));
             const double iPr1 = frcp3(1.0 + Pr);
             const bool quad = o.flags & 4;
@@ -391,19 +415,19 @@ struct CellWave {
             for (int l = 0; l < K; ++l) rc[1 + l] = G * ef[l];
         }
         lds_order();
-        double add[3];
+        // entry e: the species of slot e, whose derivative counts once for each of the side's slots it fills
+        const double v[3] = {o.em[0] * P0, o.em[1] * P1, o.em[2] * P2};
+        if (!mg.both) {
 #pragma unroll
-        for (int e = 0; e < 3; ++e) {
-            const int mk = o.em[e];
-            const double v = ((mk & 1) ? P0 : 0.0) + ((mk & 2) ? P1 : 0.0) + ((mk & 4) ? P2 : 0.0);
-            add[e] = v;
-            if (!(o.flags & (8 << e))) rc[o.ec[e]] = fma(G, o.eeff[e], v);
-        }
-        if (mg.both) {
+            for (int e = 0; e < 3; ++e) rc[o.ec[e]] = fma(G, o.eeff[e], v[e]);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 3; ++e)
+                if (!(o.flags & (8 << e))) rc[o.ec[e]] = fma(G, o.eeff[e], v[e]);
             lds_order();
 #pragma unroll
             for (int e = 0; e < 3; ++e)
-                if (o.flags & (8 << e)) rc[o.ec[e]] += add[e];
+                if (o.flags & (8 << e)) rc[o.ec[e]] += v[e];
         }
         if (lane < mg.M) {
             rc[N] = q;
@@ -474,38 +498,41 @@ struct CellWave {
     // In-place Gauss-Jordan inverse of a (2D layout) with partial pivoting: at step k the pivot is the
     // unused row of largest |a_ik|, by a 32-bit key as in the 16-lane kernel (exponent and 16 mantissa
     // bits, ties to the lowest row).  Rows are not moved while eliminating: with p_k the pivot row of
-    // step k, entry (p_k, j) ends as entry (k, p_j) of the inverse.  On return lane (r, g) holds row r
-    // of the inverse, column p_(4 i + g) in a[i]; prow = p_r; slot is the step at which row r was
-    // the pivot (16 for idle rows): the place of row r's right-hand side.
+    // step k, entry (p_k, j) ends as entry (k, p_j) of the inverse.  A pivot row is divided by its pivot
+    // only at the end (steps act on it as on its multiple), so that a step changes every row but its own
+    // pivot's in the same way.  On return lane (r, g) holds row r of the inverse, column p_(4 i + g) in a[i];
+    // prow = p_r; slot is the step at which row r was the pivot (16 for idle rows): the place of
+    // row r's right-hand side.
     __device__ __forceinline__ static void invert(double (&a)[NI], int r, int g, int &prow, int &slot) {
-        int used = (r >= N) ? -1 : 0;
-        prow = r;  // the row that becomes row r
-        slot = 16;
+        int low = (r < N) ? 15 - r : -17;  // the key's low bits; -1 - k once row r was the pivot of step k
+        double sc = 0.0;                   // 1/pivot of row r
         auto step = [&](auto kc) {
             constexpr int k = decltype(kc)::value;
             constexpr int ik = k / 4, gk = k % 4;
             const double cv = from_lane(4 * r + 64 * gk, a[ik]);
             const double inv = frcp3(cv);
-            const int key = row_max(used | ((hi32(cv) & 0x7ffffff0) | (15 - r)));
+            const int key = row_max((hi32(cv) & 0x7ffffff0) | low);
             const int pk = min(15 - (__builtin_amdgcn_readfirstlane(key) & 15), N - 1);
-            const double pinv = lane_value(inv, pk);
             const int addr = 4 * pk + 64 * g;
             double pr[NI];
 #pragma unroll
-            for (int i = 0; i < NI; ++i) pr[i] = from_lane(addr, a[i]) * pinv;
-            pr[ik] = (g == gk) ? pinv : pr[ik];
-            a[ik] = (g == gk) ? 0.0 : a[ik];
+            for (int i = 0; i < NI; ++i) pr[i] = from_lane(addr, a[i]);
             const bool piv = (r == pk);
+            const double cm = cv * -lane_value(inv, pk);
+            const double m = piv ? 0.0 : cm;
 #pragma unroll
-            for (int i = 0; i < NI; ++i) a[i] = piv ? pr[i] : fma(-cv, pr[i], a[i]);
-            used = piv ? -1 : used;
-            slot = piv ? k : slot;
-            prow = (r == k) ? pk : prow;
+            for (int i = 0; i < NI; ++i) a[i] = fma(m, pr[i], a[i]);
+            a[ik] = (g == gk) ? (piv ? 1.0 : m) : a[ik];
+            sc = piv ? inv : sc;
+            low = piv ? -1 - k : low;
         };
         each(step, std::integral_constant<int, 0>{});
+        slot = ~low;
+        const int lane0 = 64 * g;
+        prow = __builtin_amdgcn_ds_permute(lane0 + 4 * ((r < N) ? slot : r), r);
         const int addr = 4 * prow + 64 * g;
 #pragma unroll
-        for (int i = 0; i < NI; ++i) a[i] = from_lane(addr, a[i]);
+        for (int i = 0; i < NI; ++i) a[i] = from_lane(addr, a[i] * sc);
     }
     template <class F, int k>
     __device__ __forceinline__ static void each(F &f, std::integral_constant<int, k> c) {

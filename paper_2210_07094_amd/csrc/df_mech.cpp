@@ -548,19 +548,20 @@ static void pack_cell_tables(const HostMech &m, const CoopTables &ct, CellTables
             D(fSg, l) = side == 0 ? 1.0 : -1.0;
             for (int k = 0; k < K; ++k) D(fRow + k, l) = ct.ceffw[size_t(j) * K + k];
             for (int s = 0; s < 3; ++s) I(iSl + s, l) = ri[1 + 3 * side + s];
-            int fl = type == 1 ? 1 : (type == 2 ? 2 : 0), e = 0;
+            // the entry of a species lies at the first of the side's slots that it fills
+            int fl = type == 1 ? 1 : (type == 2 ? 2 : 0);
             for (int x = 0; x < kCoopEnt; ++x) {
                 const int sp = ri[7 + 2 * x], mk = ri[8 + 2 * x];
                 const int own = side == 0 ? (mk & 7) : (mk >> 3);
                 if (sp >= K || own == 0) continue;
+                const int e = (own & 1) ? 0 : (own & 2) ? 1 : 2;
                 I(iEc + e, l) = 1 + sp;
-                I(iEm + e, l) = own;
+                I(iEm + e, l) = (own & 1) + (own >> 1 & 1) + (own >> 2 & 1);
                 if (side == 1 && (mk & 7)) {
                     fl |= 8 << e;
                     t.both = 1;
                 }
                 D(fEeff + e, l) = ct.ceff[size_t(j) * KE + sp];
-                ++e;
             }
             if (quad >= 0) I(iSrc, l) = 4 * quad;
             I(iFl, l) = fl;
