@@ -62,7 +62,7 @@ df_status launch_chem_step(const MechDev &m, const StepArgs &a, int mapping, con
                            const int32_t *dcount, hipStream_t stream) {
     if (a.n == 0) return DF_OK;
     // one wave per cell wherever the mechanism's rates fit a wave's lanes (mappings 0, 2, 4 and 5): a
-    // sub-step, whose latency bounds a stiff cell, takes 18k cycles there against 40 to 47k at 16 or 32
+    // sub-step, whose latency bounds a stiff cell, takes 17k cycles there against 40 to 47k at 16 or 32
     // lanes.  Larger mechanisms: mapping 0 picks 16 lanes per cell whenever a kernel is compiled for
     // K, and with the cost order (and reaction slots that divide in two) 32 lanes for the head of
     // the order (mapping 5), whose stiffest cells then finish sooner
@@ -318,10 +318,13 @@ __global__ __launch_bounds__(256) void tape_last_length(double *tape, int K, int
 }
 
 // A queue call of so many cells that their total work sets the time and not the stiffest cell's chain: the
-// 16-lane queue, which takes the cold cells one per lane and four cells per wave otherwise, needs less work per
-// cell than one wave per cell, whose shorter chain no longer matters.  Mixing layer with local time steps, one
-// wave / 16 lanes: 262,144 cells 23.8 / 29.6 ms, 350,000 30.6 / 30.7, 450,000 36.7 / 33.5, 1,000,000 74.2 / 65.8.
-// (Static launches, whose 16-lane form waits for the slowest of four cells: 74.0 / 98.6 ms at 1,000,000.)
+// 16-lane queue, which takes four cells per wave, can be the faster one.  One wave per cell / 16 lanes, ms: mixing
+// layer with local time steps, 362,000 cells 28.2 / 31.9, 500,000 37.3 / 34.9, 1,000,000 67.4 / 65.0, 2,000,000 129 / 131;
+// developed flame, 362,000 2.15 / 2.19, 1,000,000 5.81 / 5.92; hot kernels, 362,000 11.8 / 12.2, 1,000,000 31.8 / 33.5;
+// igniting cells, 362,000 182 / 194, 700,000 353 / 377.  The line lies where the field that gains most from the
+// change gains from it, and the others lose 2 to 7 % against one wave per cell; with coop_blocks, which only the
+// 16-lane queue has, its cold cells run one per lane (the flames 1.41 and 3.80 ms).  (Static launches, whose 16-lane
+// form waits for the slowest of four cells, stay with one wave per cell: 67 / 98.6 ms for the mixing layer's 1,000,000.)
 bool work_bound_queue(const MechDev &m, int64_t n) { return n > 352 * 1024 && chem_queue_capacity(m) > 0; }
 
 // scalar dt (dts == nullptr) or per-cell dt

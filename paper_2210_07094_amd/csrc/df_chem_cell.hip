@@ -1,5 +1,5 @@
 // Detailed-chemistry step on gfx950 with one wavefront per cell, for mechanisms whose rates fit one
-// wave: at most 13 species, 32 reactions, and a group of four spare lanes per falloff reaction
+// wave: at most 31 reactions (lane 63 forms sum Y/W), and a group of four spare lanes per falloff reaction
 // (pack_cell_tables decides; larger mechanisms of the same species counts take the 16-lane kernel).
 //
 // Same integration as the other kernels (constant-pressure reactor, RODAS4, identical step-size
@@ -21,12 +21,12 @@
 //   * linear algebra: W = I/(gamma h) - J stays in that layout and is inverted in place
 //     (Gauss-Jordan with partial pivoting, three columns per lane, pivot rows fetched by lane
 //     permutation), so a stage solve is three products and two lane swaps per lane.
-// Measured on MI355X: an attempt of a lone wave takes 18.4k cycles (47k with 16 lanes per cell, whose wave
-// issues 9,000 instructions for four cells), of which right-hand sides 9k, Jacobian 4.3k, inverse 4.4k;
-// with two waves per SIMD a SIMD finishes one every 12 to 15k cycles, its vector unit busy 85 % of the
-// time with 2,400 vector instructions (1,400 of them FP64) per attempt.  Whole calls, 16 lanes -> this
-// kernel: 21 ignition cells 3.02 -> 1.35 ms, 1,001 cells 3.43 -> 1.51 ms, 65,536-cell hot-kernel field
-// 5.1-5.4 -> 2.5-2.9 ms, developed flame 0.526 -> 0.461 ms, 262,144-cell mixing layer 31 -> 23 ms.
+// Measured on MI355X: an attempt of a lone wave takes 17k cycles (47k with 16 lanes per cell, whose wave issues
+// 9,000 instructions for four cells); with two waves per SIMD a SIMD finishes one every 12k, its vector unit busy
+// 84 % of the time with 2,180 vector instructions per attempt (77 % and 2,410 per one-sub-step cell, its start and end
+// included).  Whole calls with a workspace, 16 lanes -> this kernel: 21 ignition cells 2.98 -> 1.21 ms, 1,001 cells
+// 3.40 -> 1.37 ms, 32,768 cells 19.5 -> 17.1 ms (the 16-lane queue 17.9), 65,536-cell hot-kernel field 4.97 -> 2.58 ms,
+// 65,536-cell developed flame 0.526 -> 0.416 ms, 65,536-cell mixing layer 27.6 -> 10.6 ms.
 // Every scalar that steers control flow is the same in all 64 lanes (butterfly sums), so a wave
 // never diverges.
 #include <cmath>
@@ -38,52 +38,30 @@ namespace {
 
 // The queue of the cell order.  An atomic on one address from all eight XCDs costs about 12 ns, one after
 // the other (65,536 short cells spent 340 us in them), so the order is dealt out to kCellQueues groups of
-// blocks, slot x of group s being order[s + 8 x]: neighbouring blocks run on different XCDs, so a
-// group's counter stays in one XCD's L2.  A group's units are its first quarter (the stiffest cells), and
-// in any case the first four per wave, one cell each, then four cells each.  The front waves take
-// units from the start, the others from the end: the first unit of each wave is fixed, the others are
-// claimed; a claim on top of h front and t back units is valid while h + t is below the number of units,
-// so every unit is taken once.  A wave whose group is empty goes on with the next group's units.
+// blocks, cell x of group s being order[s + 8 x]: neighbouring blocks run on different XCDs, so a
+// group's counter stays in one XCD's L2.  The front waves take cells from the start, the others from the
+// end: the first cell of each wave is fixed, the others are claimed; a claim on top of h front and t back
+// cells is valid while h + t is below the number of cells, so every cell is taken once.  A wave whose
+// group is empty goes on with the next group's cells.
 struct Queue {
     unsigned long long *ctr;  // of the group
-    int64_t n, one, units;    // cells, single-cell units, all units of the group
-    int s, fw, bw;            // group, its front and back waves
+    int n, s, fw, bw;         // cells, group, its front and back waves
 
     __device__ __forceinline__ void group(unsigned long long *base, int64_t cells, int grp, int waves) {
         s = grp;
         ctr = base + 16 * s;
-        n = (cells - s + kCellQueues - 1) / kCellQueues;
+        n = int((cells - s + kCellQueues - 1) / kCellQueues);
         const int blocks = (int(gridDim.x) - s + kCellQueues - 1) / kCellQueues;
         fw = blocks * (waves < 4 ? waves : 4);
         bw = blocks * waves - fw;
-        const int64_t w = int64_t(fw + bw) * 4;
-        one = n / 4 > w ? n / 4 : w;
-        one = one < n ? one : n;
-        units = one + (n - one + 3) / 4;
+    }
+    // the group's cell of a claim whose counter read `old` (-1: none left)
+    __device__ __forceinline__ int claimed(unsigned long long old, bool front) const {
+        const int64_t h = fw + int64_t(unsigned(__builtin_amdgcn_readfirstlane(int(old))));
+        const int64_t t = bw + int64_t(unsigned(__builtin_amdgcn_readfirstlane(int(old >> 32))));
+        return h + t >= n ? -1 : int(front ? h : n - 1 - t);
     }
 };
-// group slots [first, first + cells)
-struct Span {
-    int64_t first;
-    int cells;
-};
-__device__ __forceinline__ Span unit_span(const Queue &q, int64_t u) {
-    if (u < q.one) return {u, 1};
-    const int64_t f = q.one + (u - q.one) * 4;
-    return {f, int(f + 4 < q.n ? 4 : q.n - f)};
-}
-__device__ __forceinline__ unsigned long long claim(const Queue &q, bool front, int lane) {
-    unsigned long long old = 0;
-    if (lane == 0) old = atomicAdd(q.ctr, front ? 1ull : (1ull << 32));
-    return old;
-}
-// the unit of a claim (cells = 0: the group is empty)
-__device__ __forceinline__ Span claimed(const Queue &q, unsigned long long old, bool front) {
-    const int64_t h = q.fw + int64_t(unsigned(__builtin_amdgcn_readfirstlane(int(old))));
-    const int64_t t = q.bw + int64_t(unsigned(__builtin_amdgcn_readfirstlane(int(old >> 32))));
-    if (h + t >= q.units) return {0, 0};
-    return unit_span(q, front ? h : q.units - 1 - t);
-}
 
 constexpr int kQueueWaves = 8;  // per block of the queue: two per SIMD
 
@@ -102,103 +80,110 @@ __global__ __launch_bounds__(64 * kQueueWaves) void chem_cell_kernel(CellMech mg
     // the second wave of each SIMD works from the cold end of the order, so that the stiffest
     // cells do not share a SIMD with one another
     const bool front = wave < 4;
-    Queue u;
-    Span span = {TAPE ? cell_of_block(a.n) : int64_t(blockIdx.x) * waves + wave, 1};
+    Queue grp;
+    int64_t at = TAPE ? cell_of_block(a.n) : int64_t(blockIdx.x);  // place of the wave's cell
     if (queue) {
-        u.group(q.ctr, limit, int(blockIdx.x) % kCellQueues, waves);
-        const int64_t k = int64_t(blockIdx.x) / kCellQueues * (front ? (waves < 4 ? waves : 4) : waves - 4) +
-                          (front ? wave : wave - 4);
-        const int64_t x = front ? k : u.units - 1 - k;
-        span = (x < u.units && x >= (front ? 0 : u.fw)) ? unit_span(u, x) : Span{0, 0};
-    } else if (span.first >= limit) {
+        grp.group(q.ctr, limit, int(blockIdx.x) % kCellQueues, waves);
+        const int k = int(blockIdx.x) / kCellQueues * (front ? (waves < 4 ? waves : 4) : waves - 4) +
+                      (front ? wave : wave - 4);
+        const int x = front ? k : grp.n - 1 - k;
+        at = (x < grp.n && x >= (front ? 0 : grp.fw)) ? grp.s + int64_t(kCellQueues) * x : -1;
+    } else if (at >= limit) {
         return;
     }
-    for (int i = lane; i < C::oEff; i += 64) sh[i] = 0.0;
-    for (int i = lane; i < 32 * K; i += 64) {
-        const int j = i / K;
-        sh[C::oEff + i] = (j < mg.M) ? mg.eff[j * (K + 4) + i % K] : 0.0;
-    }
+    // (every load of the wave's start is in flight before the first is waited for)
     typename C::Row o;
     C::load_row(mg, lane, o);
+    C::load_eff(mg, lane, sh);
     Coef kc;
     kc.set();
     lds_order();
     if (lane == 0) sh[C::oC] = 1.0;
     lds_order();
-    const Opts &op = a.o;
-    const double atol = (r == 0) ? op.atol_T : op.atol_Y;
+    // The arguments, read from the kernel's argument segment where they are used: held in registers, they would push
+    // what every attempt needs out of them.
+    typedef const __attribute__((address_space(4))) StepArgs *ArgPtr;
+    const auto seg = (const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr();
+    auto args = [&]() {
+        auto p = ArgPtr(seg + (sizeof(CellMech) + alignof(StepArgs) - 1) / alignof(StepArgs) * alignof(StepArgs));
+        asm volatile("" : "+s"(p));
+        return p;
+    };
+    const double atol = (r == 0) ? a.o.atol_T : a.o.atol_Y;
     const int32_t *order = queue ? q.order : q.cidx;
     double *const yp = (r == 0) ? a.T : a.Y + int64_t(r <= K ? r - 1 : 0) * a.ld;  // the lane's row
     double *const rrp = a.rr ? a.rr + int64_t(r >= 1 && r <= K ? r - 1 : 0) * a.ld : nullptr;
-    // cell indices of a span, one per lane, and one cell's state
-    auto indices = [&](const Span &v) {
-        if (queue) return lane < v.cells ? order[u.s + kCellQueues * (v.first + lane)] : 0;
-        return order ? order[v.first] : 0;
-    };
+    // A place's cell and the cell's state.  (Loads by an index that the compiler takes for different in each lane:
+    // a scalar load would be waited for by the next LDS access.)
+    int zero = 0;
+    asm("" : "+v"(zero));
+    auto cell_at = [&](int64_t place) { return order ? order[place + zero] : int32_t(place); };
     int64_t i = 0;
     double yn = 0.0, pn = 0.0, dtn = 0.0;
-    auto fetch = [&](const Span &v, int32_t idx, int cell) {
-        i = order ? int64_t(__builtin_amdgcn_readlane(idx, cell)) : v.first;
+    auto fetch = [&](int32_t cell) {
+        const auto b = args();
+        i = int64_t(__builtin_amdgcn_readfirstlane(cell));
         if (r < N) yn = yp[i];
-        pn = a.p[i];
-        dtn = a.dts ? a.dts[i] : a.dt;
+        pn = b->p[i + zero];
+        dtn = b->dts ? b->dts[i + zero] : b->dt;
     };
-    // the next span after a unit that claimed nothing ahead; false at the end
+    auto claim = [&]() {
+        unsigned long long old = 0;
+        if (lane == 0) old = atomicAdd(grp.ctr, front ? 1ull : (1ull << 32));
+        return old;
+    };
+    auto place_of = [&](int x) { return x < 0 ? int64_t(-1) : grp.s + int64_t(kCellQueues) * x; };
+    // the next place when nothing was claimed ahead (empty: that was tried, and there is none, in this group of
+    // a queue); -1 at the end
     int left = kCellQueues - 1;  // groups not tried yet
-    auto next = [&]() {
-        if (!queue) {
-            span.first += int64_t(gridDim.x) * waves;
-            return span.first < limit;
-        }
+    auto next = [&](bool empty) {
+        if (!queue) return !empty && at + gridDim.x < limit ? at + int64_t(gridDim.x) : int64_t(-1);
         for (;;) {
-            span = claimed(u, claim(u, front, lane), front);
-            if (span.cells > 0) return true;
+            const int64_t place = empty ? -1 : place_of(grp.claimed(claim(), front));
+            if (place >= 0) return place;
+            empty = false;
             for (;;) {  // look before claiming: an empty group's counter is only read
-                if (left-- == 0) return false;
-                u.group(q.ctr, limit, (u.s + 1) % kCellQueues, waves);
-                const unsigned long long c = __hip_atomic_load(u.ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if (int64_t(c & 0xffffffffull) + int64_t(c >> 32) + u.fw + u.bw < u.units) break;
+                if (left-- == 0) return int64_t(-1);
+                grp.group(q.ctr, limit, (grp.s + 1) % kCellQueues, waves);
+                const unsigned long long c = __hip_atomic_load(grp.ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (int64_t(c & 0xffffffffull) + int64_t(c >> 32) + grp.fw + grp.bw < grp.n) break;
             }
         }
     };
-    if (span.cells == 0 && !next()) return;
-    int32_t idx = indices(span);
-    fetch(span, idx, 0);
+    if (at < 0 && (at = next(false)) < 0) return;
+    fetch(cell_at(at));
     for (;;) {
-        // a unit of several (short) cells: the next claim is in flight while they run, and each cell's
-        // state while the one before it runs; a single cell may be a long one, and claims nothing ahead
-        const int cells = span.cells;
-        const bool ahead = cells > 1;
-        const unsigned long long old = ahead ? claim(u, front, lane) : 0;
-        Span span2 = {0, 0};
-        int32_t idx2 = 0;
-        for (int cell = 0; cell < cells; ++cell) {
+        // The cell that follows is claimed when an attempt starts that would end this one, and its index and
+        // state are loaded while that attempt's stages run; a chain that goes on holds no other cell back.  With a
+        // claim after each single cell, and four cells per claim in the order's colder part, small flames waited for
+        // them (24,000 cells 212 us, now 173; 16 lanes 202) and uniformly stiff fields for the last units (32,768
+        // ignition cells 22.4 ms, now 17.1).
+        enum { kNone, kClaimed, kIndexed, kLoaded, kEmpty };
+        int ahead = kNone;
+        unsigned long long old = 0;
+        int32_t following = 0;
+        {
             const int64_t ic = i;
+            const auto b = args();
             typename C::Cell c;
             double yr = yn;
             c.p = pn;
             const double dtc = dtn;
-            if (ahead && cell == cells - 2) {
-                span2 = claimed(u, old, front);
-                idx2 = indices(span2);
-            }
-            if (cell + 1 < cells)
-                fetch(span, idx, cell + 1);
-            else if (span2.cells > 0)
-                fetch(span2, idx2, 0);
             // non-finite rows, T <= 0, p or dt unusable: left untouched
             const bool bad = !isfinite(yr) || (r == 0 && !(yr > 0.0)) || !isfinite(c.p) || !(c.p > 0.0) ||
                              !isfinite(dtc) || !(dtc > 0.0);
             if (__builtin_amdgcn_ballot_w64(bad) != 0ull) {
                 if (lane == 0) {
-                    if (a.status) a.status[ic] = DF_CELL_NONFINITE;
-                    if (a.nsteps) {
-                        a.nsteps[ic] = 0;
-                        a.nsteps[a.n + ic] = 0;
+                    if (b->status) b->status[ic] = DF_CELL_NONFINITE;
+                    if (b->nsteps) {
+                        b->nsteps[ic] = 0;
+                        b->nsteps[b->n + ic] = 0;
                     }
-                    if (TAPE) Tape(K, a.n, a.tape_cap).count(a.tape)[ic] = -1;
+                    if (TAPE) Tape(K, b->n, b->tape_cap).count(b->tape)[ic] = -1;
                 }
-                if (a.rr && lane >= 1 && lane <= K) rrp[ic] = 0.0;
+                if (b->rr && lane >= 1 && lane <= K) rrp[ic] = 0.0;
+                if ((at = next(false)) < 0) return;
+                fetch(cell_at(at));
                 continue;
             }
             c.ip = frcp(c.p);
@@ -206,20 +191,21 @@ __global__ __launch_bounds__(64 * kQueueWaves) void chem_cell_kernel(CellMech mg
             c.lc6p = dlogp(kc, c.c6p);
             const double y0 = yr;
             double rho0 = 0.0;
-            if (a.rr) {  // input density over dt, for rr
+            if (b->rr) {  // input density over dt, for rr
                 const double sYW = row_sum((r == 0) ? 0.0 : yr * o.iW);
                 rho0 = fdiv(c.p, sYW * kR * lane_value(yr, 0) * dtc);
             }
-            const double h_in = a.h_io ? a.h_io[ic] : 0.0;
+            const double h_in = b->h_io ? b->h_io[ic] : 0.0;
             bool fresh = !(h_in > 0.0);
             double h = fresh ? 0.0 : fmin(h_in, dtc);
-            if (!fresh && !(h >= op.h_min)) h = op.h_min;
+            if (!fresh && !(h >= b->o.h_min)) h = b->o.h_min;
             double t = 0.0, h_final = 0.0;
             int acc = 0, rej = 0;
             bool prev_rej = false;
             int st;
             for (;;) {
-                if (acc + rej >= op.max_steps) {
+                const auto e = args();
+                if (acc + rej >= e->o.max_steps) {
                     st = DF_CELL_MAX_STEPS;
                     break;
                 }
@@ -227,15 +213,19 @@ __global__ __launch_bounds__(64 * kQueueWaves) void chem_cell_kernel(CellMech mg
                 const double f0 = C::jacobian(mg, kc, o, c, sh, lane, r, g, yr, w);
                 if (fresh) {
                     // initial sub-step from the weighted norms of y0 and f(y0)
-                    const double isc = frcp(atol + op.rtol * fabs(yr));
+                    const double isc = frcp(atol + e->o.rtol * fabs(yr));
                     const double qy = (r < N) ? yr * isc : 0.0, qf = (r < N) ? f0 * isc : 0.0;
                     const double ny = lane_value(row_sum(qy * qy), 0), nf = lane_value(row_sum(qf * qf), 0);
                     h = (nf > 0.0) ? fmin(0.01 * sqrt(ny / nf), dtc) : dtc;
-                    if (!(h >= op.h_min)) h = op.h_min;
+                    if (!(h >= e->o.h_min)) h = e->o.h_min;
                     fresh = false;
                 }
                 const bool last = (t + h >= dtc);
                 const double ht = last ? dtc - t : h;
+                if (last && ahead == kNone) {
+                    if (queue) old = claim();
+                    ahead = kClaimed;
+                }
                 const double ih = frcp(ht), ig = ih * (1.0 / Rodas4::g);
 #pragma unroll
                 for (int j = 0; j < NI; ++j) w[j] = ((4 * j + g == r && r < N) ? ig : 0.0) - w[j];
@@ -246,6 +236,15 @@ __global__ __launch_bounds__(64 * kQueueWaves) void chem_cell_kernel(CellMech mg
 #pragma unroll
                 for (int s = 0; s < 6; ++s) {
                     double fs = f0;
+                    if (s == 2 && ahead == kClaimed) {
+                        at = queue ? place_of(grp.claimed(old, front)) : next(false);
+                        if (at >= 0) following = cell_at(at);
+                        ahead = at >= 0 ? kIndexed : kEmpty;
+                    }
+                    if (s == 4 && ahead == kIndexed) {
+                        fetch(following);
+                        ahead = kLoaded;
+                    }
                     if (s > 0) {
                         ysr = yr;
 #pragma unroll
@@ -265,34 +264,36 @@ __global__ __launch_bounds__(64 * kQueueWaves) void chem_cell_kernel(CellMech mg
                 }
                 // y_new = (stage-6 state) + u6 ; error = u6
                 const double ynr = ysr + u[5];
-                const double sc = atol + op.rtol * fmax(fabs(yr), fabs(ynr));
-                const double er = (r < N) ? fdiv(u[5], sc) : 0.0;
-                const double err = lane_value(sqrt(row_sum(er * er) * (1.0 / N)), 0);
+                const double sc = atol + e->o.rtol * fmax(fabs(yr), fabs(ynr));
+                const double er = (r < N) ? u[5] * frcp3(sc) : 0.0;
+                const double e2 = lane_value(row_sum(er * er) * (1.0 / N), 0);  // squared norm
                 const double fmx = prev_rej ? 1.0 : 6.0;
-                double fac;
-                if (!isfinite(err))
-                    fac = 0.2;
-                else if (err == 0.0)
-                    fac = fmx;
-                else
-                    fac = fmin(fmx, fmax(0.2, 0.9 / sqrt(sqrt(err))));  // 0.9 err^(-1/4)
-                if (isfinite(err) && err <= 1.0) {
+                // 0.9 err^(-1/4) = 0.9 e2^(-1/8) from three reciprocal square root estimates and a Newton step,
+                // within [0.2, fmx] (reached below 1e-12)
+                double fac = 0.2;
+                if (isfinite(e2)) {
+                    const double x = fmax(e2, 1e-12);
+                    const double v = __builtin_amdgcn_rsq(__builtin_amdgcn_rsq(__builtin_amdgcn_rsq(x)));
+                    const double v2 = v * v, v4 = v2 * v2;
+                    fac = fmin(fmx, fmax(0.2, 0.9 * fma(v, fma(-0.125 * x * v4, v4, 0.125), v)));
+                }
+                if (isfinite(e2) && e2 <= 1.0) {
                     if (TAPE) {
                         int pc[NI];
 #pragma unroll
                         for (int j = 0; j < NI; ++j) pc[j] = __builtin_amdgcn_ds_bpermute(4 * (4 * j + g), prow);
-                        if (acc < a.tape_cap && r < N) {
+                        if (acc < e->tape_cap && r < N) {
                             // the accepted sub-step for the adjoint
-                            const Tape tp(K, a.n, a.tape_cap);
+                            const Tape tp(K, e->n, e->tape_cap);
                             const int64_t s = acc;
 #pragma unroll
                             for (int j = 0; j < NI; ++j)
-                                if (4 * j + g < N) a.tape[tp.w(s, r * N + pc[j]) + ic] = w[j];
+                                if (4 * j + g < N) e->tape[tp.w(s, r * N + pc[j]) + ic] = w[j];
                             if (g == 0) {
-                                a.tape[tp.y(s, r) + ic] = yr;
-                                if (r == 0 && !(queue && s == a.tape_cap - 1)) a.tape[tp.h(s) + ic] = ht;
+                                e->tape[tp.y(s, r) + ic] = yr;
+                                if (r == 0 && !(queue && s == e->tape_cap - 1)) e->tape[tp.h(s) + ic] = ht;
 #pragma unroll
-                                for (int si = 0; si < 6; ++si) a.tape[tp.u(s, si * N + r) + ic] = u[si];
+                                for (int si = 0; si < 6; ++si) e->tape[tp.u(s, si * N + r) + ic] = u[si];
                             }
                         }
                     }
@@ -314,38 +315,34 @@ __global__ __launch_bounds__(64 * kQueueWaves) void chem_cell_kernel(CellMech mg
                     ++rej;
                     prev_rej = true;
                     h = ht * fac;
-                    if (h < op.h_min) {
+                    if (h < e->o.h_min) {
                         st = DF_CELL_H_UNDERFLOW;
                         break;
                     }
                 }
             }
             __builtin_amdgcn_s_setprio(0);
+            const auto e = args();
             if (TAPE) {
                 // a cell whose accepted sub-steps did not all fit keeps its result but has no tape
-                if (st == DF_CELL_OK && acc > a.tape_cap) st = DF_CELL_TAPE_FULL;
-                if (lane == 0) Tape(K, a.n, a.tape_cap).count(a.tape)[ic] = (st == DF_CELL_OK) ? acc : -1;
+                if (st == DF_CELL_OK && acc > e->tape_cap) st = DF_CELL_TAPE_FULL;
+                if (lane == 0) Tape(K, e->n, e->tape_cap).count(e->tape)[ic] = (st == DF_CELL_OK) ? acc : -1;
             }
             if (lane < N) yp[ic] = yr;
             if (lane == 0) {
-                if (a.h_io) a.h_io[ic] = (st == DF_CELL_OK) ? h_final : h;
-                if (a.status) a.status[ic] = (st == DF_CELL_OK) ? a.status_ok : st;
-                if (a.nsteps) {
-                    a.nsteps[ic] = acc;
-                    a.nsteps[a.n + ic] = rej;
+                if (e->h_io) e->h_io[ic] = (st == DF_CELL_OK) ? h_final : h;
+                if (e->status) e->status[ic] = (st == DF_CELL_OK) ? e->status_ok : st;
+                if (e->nsteps) {
+                    e->nsteps[ic] = acc;
+                    e->nsteps[e->n + ic] = rej;
                 }
-            } else if (lane <= K && a.rr) {
+            } else if (lane <= K && e->rr) {
                 rrp[ic] = rho0 * (yr - y0);
             }
         }
-        if (span2.cells > 0) {
-            span = span2;
-            idx = idx2;
-            continue;
-        }
-        if (!next()) return;
-        idx = indices(span);
-        fetch(span, idx, 0);
+        if (ahead == kLoaded) continue;
+        if ((at = next(ahead == kEmpty)) < 0) return;
+        fetch(cell_at(at));
     }
 }
 
