@@ -72,6 +72,7 @@ __global__ __launch_bounds__(64 * kQueueWaves) void chem_cell_kernel(CellMech mg
     using C = CellWave<K, EL>;
     constexpr int N = C::N, NI = C::NI;
     extern __shared__ double lds[];
+    __shared__ int taken;
     const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6), waves = int(blockDim.x) >> 6;
     double *const sh = lds + wave * C::kEnd;
@@ -81,13 +82,31 @@ __global__ __launch_bounds__(64 * kQueueWaves) void chem_cell_kernel(CellMech mg
     // cells do not share a SIMD with one another
     const bool front = wave < 4;
     Queue grp;
+    // Without a queue: one cell per one-wave block, or (several waves) a block takes one cell of each run of gridDim.x
+    // cells, another place in each run, so that a hot column of a field meets every block, and its waves
+    // share them out through a counter in LDS.  One wave per cell for any number of cells, whose start (its rows of
+    // the mechanism) a one-sub-step cell pays a sixth of its time for: flame of 8,000 cells 75 us, 65,536 cells
+    // 522 us, this way 60 and 394 us (16 lanes 65 and 476); hot-kernel field of 65,536 cells 5.4 and 3.5 ms (10.3).
+    const bool local = !queue && waves > 1;
     int64_t at = TAPE ? cell_of_block(a.n) : int64_t(blockIdx.x);  // place of the wave's cell
+    auto local_place = [&]() {
+        int x = 0;
+        if (lane == 0) x = atomicAdd(&taken, 1);
+        x = __builtin_amdgcn_readfirstlane(x);
+        const unsigned grid = gridDim.x;
+        const int64_t place = int64_t(x) * grid + (blockIdx.x + unsigned(x) * 37u) % grid;
+        return place < limit ? place : int64_t(-1);
+    };
     if (queue) {
         grp.group(q.ctr, limit, int(blockIdx.x) % kCellQueues, waves);
         const int k = int(blockIdx.x) / kCellQueues * (front ? (waves < 4 ? waves : 4) : waves - 4) +
                       (front ? wave : wave - 4);
         const int x = front ? k : grp.n - 1 - k;
         at = (x < grp.n && x >= (front ? 0 : grp.fw)) ? grp.s + int64_t(kCellQueues) * x : -1;
+    } else if (local) {
+        if (threadIdx.x == 0) taken = 0;
+        __syncthreads();
+        if ((at = local_place()) < 0) return;
     } else if (at >= limit) {
         return;
     }
@@ -137,7 +156,7 @@ __global__ __launch_bounds__(64 * kQueueWaves) void chem_cell_kernel(CellMech mg
     // a queue); -1 at the end
     int left = kCellQueues - 1;  // groups not tried yet
     auto next = [&](bool empty) {
-        if (!queue) return !empty && at + gridDim.x < limit ? at + int64_t(gridDim.x) : int64_t(-1);
+        if (!queue) return local && !empty ? local_place() : int64_t(-1);
         for (;;) {
             const int64_t place = empty ? -1 : place_of(grp.claimed(claim(), front));
             if (place >= 0) return place;
@@ -348,21 +367,15 @@ __global__ __launch_bounds__(64 * kQueueWaves) void chem_cell_kernel(CellMech mg
 
 template <int K, int EL>
 df_status launch_k(const MechDev &m, const StepArgs &a, const CellQueue &q, hipStream_t stream) {
-    // the queue runs a persistent grid, one block of two waves per SIMD and compute unit, with as
-    // many front waves as there are SIMDs; a device-side count a grid of single waves that stride over
-    // it; otherwise one cell per block, so that the hardware balances the cells
+    // the queue, and calls without an order of more cells than waves fit at once, run a persistent grid, one
+    // block of two waves per SIMD and compute unit (the queue with as many front waves as there are SIMDs);
+    // otherwise one cell per wave
     int dev = 0, cus = 0, waves = 1;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
         return fail(DF_E_HIP, "chem_step: cannot read the device's compute units");
-    int64_t blocks = a.n;
-    if (q.ctr) {
-        waves = a.n <= int64_t(cus) * 4 ? 1 : kQueueWaves;
-        blocks = waves == 1 ? a.n : cus;
-    } else if (q.dcount) {
-        blocks = blocks < int64_t(cus) * 8 ? blocks : int64_t(cus) * 8;
-    }
-    blocks = blocks < max_blocks(64) ? blocks : max_blocks(64);  // (beyond, the blocks stride)
+    if (a.n > int64_t(cus) * (q.ctr ? 4 : kQueueWaves)) waves = kQueueWaves;
+    const int64_t blocks = waves == 1 ? a.n : cus;
     const size_t lds = size_t(waves) * CellWave<K, EL>::kEnd * sizeof(double);
     const CellMech cm{m.xd, m.xi, m.ceff, m.M, m.xtroe, m.xboth};
     if (a.tape)

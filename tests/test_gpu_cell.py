@@ -212,3 +212,30 @@ def test_queue_of_many_cells(h2_path, h2_mech, n):
         worst, flipped, tol_err = compare(b, a)
         assert worst <= 1e-8, worst
         assert flipped <= n // 500 and tol_err <= 10.0, (flipped, tol_err)
+
+
+@pytest.mark.parametrize("n, out", [(300, 0), (300, 300), (2049, 1), (5000, 257), (5000, 4999)])
+def test_fallback_list(h2_path, h2_mech, tmp_path, n, out):
+    """Cells outside the training box of a DNN step reach the kernel through a list whose length is known on the
+    device only: none, a few, more than the blocks of the launch, all but one; the bits of a plain step."""
+    import torch
+    import paper_2210_07094_amd as df
+    from test_gpu_dnn import _net
+    K = 9
+    _net(tmp_path / "n.dfdnn", hidden=(160,), box=(np.full(K + 2, -1e300), np.r_[1e300, 2e5, np.full(K, 1e300)]))
+    gm = df.Mechanism(h2_path)
+    dnn = df.DNN(tmp_path / "n.dfdnn", gm)
+    f = fields.ignition_cells(h2_mech, n=n, seed=n)
+    pick = np.random.default_rng(out).permutation(n)[:out]
+    f["p"][pick] = 3e5  # beyond the box
+    print(f"case: {out} of {n} cells outside the box", flush=True)
+    t = {k: torch.tensor(np.ascontiguousarray(f[k]), device="cuda:0") for k in ("T", "p", "Y")}
+    st = torch.full((n,), -7, dtype=torch.int32, device="cuda:0")
+    dnn.step(t["T"], t["p"], t["Y"], 1e-6, status=st)
+    torch.cuda.synchronize()
+    st = st.cpu().numpy()
+    assert np.all(st[pick] == df.CELL_DNN_FALLBACK) and np.all(np.delete(st, pick) == df.CELL_OK)
+    if out:
+        ref = _step(gm, {"T": f["T"][pick], "p": f["p"][pick], "Y": np.ascontiguousarray(f["Y"][:, pick])}, 1e-6, False)
+        np.testing.assert_array_equal(t["T"].cpu().numpy()[pick], ref["T"])
+        np.testing.assert_array_equal(t["Y"].cpu().numpy()[:, pick], ref["Y"])
