@@ -568,7 +568,6 @@ __global__ __launch_bounds__(256) void sum_cells_kernel(const double *__restrict
     if (t == 0) out[src[j]] = part_sum[0];
 }
 
-// per-cell ln A adjoints, then the order of the one-wave-per-cell sweep
 // The per-cell ln A gradients, and after them the sweep's cell order.  The order is optional: a workspace of the
 // gradients alone is accepted, and the sweep then takes the cells by index.
 size_t adj_ws_min_bytes(int M, int64_t n) { return size_t(8) * size_t(M) * size_t(n); }

@@ -416,14 +416,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1))) void
     extern __shared__ double sh[];
     const int lane = threadIdx.x, r = lane & 15, g = lane >> 4;
     const int64_t slot = a.first + blockIdx.x, i = a.order ? int64_t(a.order[slot]) : slot;
-    for (int e = lane; e < S::kSize; e += 64) sh[e] = 0.0;
-    lds_order();
-    for (int e = lane; e < 32 * K; e += 64) {
-        const int j = e / K;
-        sh[C::oEff + e] = (j < mg.M) ? mg.eff[j * (K + 4) + e % K] : 0.0;
-    }
+    for (int e = C::kEnd + lane; e < S::kSize; e += 64) sh[e] = 0.0;
     typename C::Row o;
     C::load_row(mg, lane, o);
+    C::load_eff(mg, lane, sh);
     typename S::Lists l;
 #pragma unroll
     for (int e = 0; e < kLS; ++e) {
@@ -461,17 +457,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1))) void
         hn = T[tp.h(s)];
     };
     if (cnt > 0) load(cnt - 1);
-    int prio = 0;
     for (int64_t s = int64_t(cnt) - 1; s >= 0; --s) {
-        // of the two waves of a SIMD the one with more sub-steps left issues first
-        const int pr = s >= 512 ? 3 : (s >= 256 ? 2 : (s >= 128 ? 1 : 0));
-        if (pr != prio) {
-            prio = pr;
-            if (pr == 3) __builtin_amdgcn_s_setprio(3);
-            if (pr == 2) __builtin_amdgcn_s_setprio(2);
-            if (pr == 1) __builtin_amdgcn_s_setprio(1);
-            if (pr == 0) __builtin_amdgcn_s_setprio(0);
-        }
         double w[NI], ub[6], u[5];
 #pragma unroll
         for (int j = 0; j < NI; ++j) w[j] = wn[j];
@@ -539,7 +525,7 @@ df_status launch_k(const MechDev &m, SweepArgs a, hipStream_t s) {
 }  // namespace
 
 // (the adjoint takes at most 24 reactions, which six list entries per lane cover)
-bool sweep_cell_supported(const MechDev &m) { return m.xel == 6 && m.xad; }
+bool sweep_cell_supported(const MechDev &m) { return m.xel == 6 && m.xad && chem_cell_supported(m); }
 
 df_status launch_sweep_cell(const MechDev &m, int64_t n, int64_t ld, const double *p, const double *tape, int32_t cap,
                             const double *Tb, const double *Yb, double *T0b, double *Y0b, double *thc, double *wth,

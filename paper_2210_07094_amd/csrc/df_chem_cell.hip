@@ -391,7 +391,13 @@ df_status launch_k(const MechDev &m, const StepArgs &a, const CellQueue &q, hipS
 
 }  // namespace
 
-bool chem_cell_supported(const MechDev &m) { return m.xel != 0; }
+bool chem_cell_supported(const MechDev &m) {
+    bool compiled = false;
+#define DF_CASE(k) compiled = compiled || m.K == k;
+    DF_CHEM_SPECIES_LIST(DF_CASE)
+#undef DF_CASE
+    return compiled && m.xel != 0;
+}
 
 df_status launch_chem_cell(const MechDev &m, const StepArgs &a, const CellQueue &q, hipStream_t stream) {
     if (a.n == 0) return DF_OK;

@@ -132,7 +132,7 @@ struct StepArgs {
     int32_t *status, *nsteps;
     Opts o;
     int32_t status_ok;  // status written for cells that succeed (DF_CELL_OK or DF_CELL_DNN_FALLBACK)
-    // tape of the accepted sub-steps for the adjoint (16-lane launch only; nullptr = none),
+    // tape of the accepted sub-steps for the adjoint (one-wave-per-cell and 16-lane launches; nullptr = none),
     // layout in Tape below
     double *tape = nullptr;
     int32_t tape_cap = 0;
@@ -210,8 +210,8 @@ bool chem_coop_supported(const MechDev &m);
 df_status launch_chem_coop(const MechDev &m, const StepArgs &a, const CellQueue &q, hipStream_t stream,
                            int halves = 1);
 // one wavefront per cell for small mechanisms (df_chem_cell.hip); q.ctr with q.order: cells claimed
-// from the order, else slot s < *dcount (or n) takes cell cidx[s] (or s); writes the tape when given
-// its queue's counters: kCellQueues of them, 128 bytes apart, zero at the launch
+// from the order, else slot s < *dcount (or n) takes cell cidx[s] (or s); writes the tape when given.
+// The queue's counters: kCellQueues of them, 128 bytes apart, zero at the launch
 constexpr int kCellQueues = 8;
 // A launch holds fewer than 2^32 threads.  Kernels with one wave or block per cell start at most this many of
 // `threads` threads and stride over the rest.

@@ -457,7 +457,7 @@ static void pack_wave_tables(const HostMech &m, const CoopTables &ct, WaveTables
 }
 
 // Per-lane rows of the one-wave-per-cell kernel for small mechanisms (fields as its load_row reads
-// them, field f of lane l at 64 f + l).  el = 0 where the mechanism does not fit: more than 32
+// them, field f of lane l at 64 f + l).  el = 0 where the mechanism does not fit: more than 31
 // reactions, a species in more reactions than four lists hold, or too few spare lanes for the
 // falloff reactions' quads (lanes beyond M in either half, aligned to four) and lane 63, whose row
 // of weights 1/W_k gives sum Y/W.

@@ -6,8 +6,8 @@
 // Block tile 128 x 160 with four wave64s in a 2 x 2 arrangement, each wave
 // owning a 64 x 80 sub-tile (4 x 5 MFMA tiles); operands are staged through
 // LDS 64 deep in K by loads that write LDS directly, one or three stages ahead
-// of the MFMAs.  The MFMAs take the weight
-// fragment as their first operand, so that each lane ends with four consecutive
+// of the MFMAs.  The MFMAs take the weight fragment as their first operand, so
+// that each lane ends with four consecutive
 // outputs of one row, converted with one packed bf16 conversion pair: the GELU
 // epilogues (inference, with GELU from an LDS table, and the training forward and
 // backward) stage them per wave in LDS and write 16-byte row pieces.  Tiles sharing
@@ -703,9 +703,9 @@ __global__ __launch_bounds__(kThreads, NST == 2 ? 2 : 1) void gemm_fp8_kernel(co
             finish(std::integral_constant<int, 0>{});
         __syncthreads();
         // half of the rows for each of the two waves
-            stage_flush<WM / 2>(stg + wn * (WM / 2 * kStgStrideB),
-                                reinterpret_cast<uint8_t *>(C) + (row0 + wm * WM + wn * (WM / 2)) * int64_t(ldc) + col0,
-                                ldc, lane);
+        stage_flush<WM / 2>(stg + wn * (WM / 2 * kStgStrideB),
+                            reinterpret_cast<uint8_t *>(C) + (row0 + wm * WM + wn * (WM / 2)) * int64_t(ldc) + col0,
+                            ldc, lane);
     } else {
         uint8_t *const stg = St0 + w * (32 * kStgStrideB);
         const int64_t ldb_c = 2 * int64_t(ldc);
