@@ -102,8 +102,8 @@ typedef struct {
     int32_t coop_blocks; /* queue schedule: waves that start as 16-lane groups; the others start
                             one cell per lane on the cold cells and then join the groups.
                             0 (default) all resident waves, -1 none, k > 0 k waves (capped at
-                            the resident count); df_chem_autotune picks it; ignored where one
-                            wavefront per cell runs */
+                            the resident count); df_chem_autotune picks it.  Where one wavefront per
+                            cell would run, 0 and calls of up to 40,960 cells keep that */
 } df_chem_opts;
 
 /* DNN options. */

@@ -327,6 +327,14 @@ __global__ __launch_bounds__(256) void tape_last_length(double *tape, int K, int
 // form waits for the slowest of four cells, stay with one wave per cell: 67 / 98.6 ms for the mixing layer's 1,000,000.)
 bool work_bound_queue(const MechDev &m, int64_t n) { return n > 352 * 1024 && chem_queue_capacity(m) > 0; }
 
+// A queue call that asks for waves of cold cells one per lane (coop_blocks other than 0) gets them from as many
+// cells on as they can pay: one wave per cell / per-lane cold cells, developed flame of 32,768 cells 222 / 255 us,
+// 65,536 cells 413 / 308 us, 350,000 cells 2.05 / 1.37 ms.  (Fields with few cold or many stiff cells are better off
+// without: mixing layer of 65,536 cells 10.7 / 31 ms.  The option is the caller's or the autotuner's.)
+bool lanes_queue(const MechDev &m, const df_chem_opts &o, int64_t n) {
+    return o.coop_blocks != 0 && n > 40 * 1024 && chem_queue_capacity(m) > 0;
+}
+
 // scalar dt (dts == nullptr) or per-cell dt
 df_status chem_step_impl(const char *who, const df_mech *mech, int64_t n_cells, int64_t ld, double dt,
                          const double *dts, const double *p, double *T, double *Y, double *h_inout, double *rr,
@@ -357,7 +365,8 @@ df_status chem_step_impl(const char *who, const df_mech *mech, int64_t n_cells, 
     if (workspace) st = order_cells(a, wk, s);
     if (st == DF_OK) {
         if (workspace && chem_cell_supported(mech->dev) &&
-            (o.schedule == 2 ? !work_bound_queue(mech->dev, n_cells) : (o.mapping != 1 && o.mapping != 3))) {
+            (o.schedule == 2 ? !(work_bound_queue(mech->dev, n_cells) || lanes_queue(mech->dev, o, n_cells))
+                             : (o.mapping != 1 && o.mapping != 3))) {
             st = launch_chem_cell(mech->dev, a, CellQueue{nullptr, nullptr, wk.idx, wk.groups, nullptr, 0}, s);
         } else if (o.schedule == 2) {
             const int32_t cap = chem_queue_capacity(mech->dev);
@@ -542,9 +551,14 @@ extern "C" df_status df_chem_autotune(const df_mech *mech, int64_t n_cells, int6
     void *ows = base;
     auto *Tc = reinterpret_cast<double *>(base + order_bytes(n_cells));
     auto *Yc = reinterpret_cast<double *>(base + order_bytes(n_cells) + al256(size_t(n_cells) * 8));
-    // with one wave per cell every queue schedule and the 16- and 32-lane mappings are the same launch
+    // with one wave per cell the 16- and 32-lane mappings are the same launch, and so are the queue schedules up to
+    // the cell counts of the two rules above
     const bool cell = chem_cell_supported(mech->dev);
-    const int32_t cap = (cell && !work_bound_queue(mech->dev, n_cells)) ? 0 : chem_queue_capacity(mech->dev);
+    df_chem_opts lanes = *opts;
+    lanes.coop_blocks = 1;
+    const bool queue = !cell || work_bound_queue(mech->dev, n_cells);
+    const int32_t cap =
+        queue || lanes_queue(mech->dev, lanes, n_cells) ? chem_queue_capacity(mech->dev) : 0;
     struct Cand {
         int32_t schedule, coop_blocks, mapping;
     };
@@ -566,7 +580,7 @@ extern "C" df_status df_chem_autotune(const df_mech *mech, int64_t n_cells, int6
     }
     if (lane_kernel && (opts->mapping == 0 || opts->mapping == 2)) cands.push_back({1, 0, 1});
     if (cap > 0) {
-        cands.push_back({2, 0, opts->mapping});
+        if (queue) cands.push_back({2, 0, opts->mapping});
         cands.push_back({2, cap / 2, opts->mapping});
         cands.push_back({2, (3 * cap) / 4, opts->mapping});
     }

@@ -97,3 +97,29 @@ def test_autotune(wide):
     ro = om.chem_step(f["T"], f["p"], f["Y"], f["dt"], h_inout=np.zeros(f["T"].size))
     worst, flipped, tol_err = compare(g, ro)
     assert worst <= RTOL_PARITY and flipped <= 3 and tol_err <= 10.0
+
+
+@pytest.mark.parametrize("n", [40 * 1024, 40 * 1024 + 1])
+def test_cold_cells_per_lane_of_a_mechanism_that_fits_a_wave(h2_path, h2_mech, n):
+    """Where a queue call with coop_blocks leaves one wave per cell (the bits of the static launch) for 16-lane groups
+    and cold cells one per lane (the parity bar against it)."""
+    import paper_2210_07094_amd as df
+    gm = df.Mechanism(h2_path)
+    c = _cells(h2_mech, n=1001)
+    c["T"][500:] = np.linspace(300.0, 490.0, 501)
+    f = {k: np.resize(c[k], n) for k in ("T", "p", "dt")}
+    f["Y"] = np.ascontiguousarray(c["Y"][:, np.arange(n) % 1001])
+    f["dt"] = f["dt"] * 0.02
+    print(f"case: {n} cells", flush=True)
+    a = _run(gm, f, df.chem_opts())
+    for blocks in (8, -1):
+        print(f"case: coop_blocks {blocks}", flush=True)
+        b = _run(gm, f, df.chem_opts(schedule=2, coop_blocks=blocks))
+        assert np.array_equal(a["status"], b["status"]) and np.all(a["status"] == df.CELL_OK)
+        if n <= 40 * 1024:
+            for k in ("T", "Y", "n_acc", "n_rej"):
+                assert np.array_equal(a[k], b[k]), k
+        else:
+            worst, flipped, tol_err = compare(b, a)
+            assert worst <= RTOL_PARITY, worst
+            assert flipped <= n // 500 and tol_err <= 10.0, (flipped, tol_err)
