@@ -131,8 +131,8 @@ def dnn_error(T0, Y0, Td, Yd, To, Yo, status):
 def batching_study(gm, mech_h, dev):
     """Uneven stiffness: the 100^3 = 1,000,000-cell mixing layer with a step length per cell
     (log-uniform 1e-7..1e-5 s), integrated with the naive schedule (one launch, one cell per
-    lane, index order), the static 16-lane schedule in cost order, and the schedule the
-    autotuner picks (persistent work queue for this workload)."""
+    lane, index order), the static schedule in cost order (automatic mapping: one wavefront per
+    cell), and the schedule the autotuner picks (persistent work queue for this workload)."""
     import torch
     import paper_2210_07094_amd as df
     from synth import fields
@@ -161,7 +161,7 @@ def batching_study(gm, mech_h, dev):
         return float(min(ms))
 
     naive = timed(df.chem_opts(schedule=1, mapping=1), False, 1)
-    static = timed(df.chem_opts(schedule=1, mapping=2), True, 2)
+    static = timed(df.chem_opts(schedule=1), True, 2)
     tuned = gm.autotune(T0, p, Y0, dts)
     queue = timed(tuned, True, 3)
     nsh = ns.cpu().numpy()
@@ -169,7 +169,7 @@ def batching_study(gm, mech_h, dev):
                         "dt per cell log-uniform 1e-7..1e-5 s", "n_cells": n,
             "attempts_total": int(nsh.sum()), "accepted_max": int(nsh[:n].max()),
             "status_counts": np.bincount(st.cpu().numpy()).tolist(),
-            "naive_one_cell_per_lane_ms": naive, "static_16_lanes_cost_order_ms": static,
+            "naive_one_cell_per_lane_ms": naive, "static_cost_order_ms": static,
             "autotuned": {"schedule": int(tuned.schedule), "coop_blocks": int(tuned.coop_blocks), "ms": queue},
             "cells_per_s_autotuned": n / (queue * 1e-3), "speedup_vs_naive": naive / queue}
 
@@ -199,7 +199,7 @@ def adjoint_lane_ops(mech, ops):
 
 def adjoint_study(gm, mech_h, dev, with_cpu, threads):
     """Differentiation workload: 4096 cells, T0 1000-1600 K, phi 0.5-2, p = 1 atm, dt = 1e-5 s.
-    The taped step (16 lanes per cell, recording the stage tape), one reverse sweep (the
+    The taped step (one wavefront per cell, recording the stage tape), one reverse sweep (the
     gradient of a scalar loss with respect to T0, Y0 and every ln A), and the full 10 x 34
     Jacobian per cell (one sweep per output component); the oracle's forward sensitivities
     (complex-step differentiation of its replay) on a sample of cells for the CPU rate."""
