@@ -329,7 +329,7 @@ bool work_bound_queue(const MechDev &m, int64_t n) { return n > 352 * 1024 && ch
 
 // A queue call that asks for waves of cold cells one per lane (coop_blocks other than 0) gets them from as many
 // cells on as they can pay: one wave per cell / per-lane cold cells, developed flame of 32,768 cells 222 / 255 us,
-// 65,536 cells 413 / 308 us, 350,000 cells 2.05 / 1.37 ms.  (Fields with few cold or many stiff cells are better off
+// 65,536 cells 405 / 308 us, 350,000 cells 2.05 / 1.37 ms.  (Fields with few cold or many stiff cells are better off
 // without: mixing layer of 65,536 cells 10.7 / 31 ms.  The option is the caller's or the autotuner's.)
 bool lanes_queue(const MechDev &m, const df_chem_opts &o, int64_t n) {
     return o.coop_blocks != 0 && n > 40 * 1024 && chem_queue_capacity(m) > 0;

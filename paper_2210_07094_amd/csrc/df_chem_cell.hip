@@ -26,7 +26,7 @@
 // 84 % of the time with 2,180 vector instructions per attempt (77 % and 2,410 per one-sub-step cell, its start and end
 // included).  Whole calls with a workspace, 16 lanes -> this kernel: 21 ignition cells 2.98 -> 1.21 ms, 1,001 cells
 // 3.40 -> 1.37 ms, 32,768 cells 19.5 -> 17.1 ms (the 16-lane queue 17.9), 65,536-cell hot-kernel field 4.97 -> 2.58 ms,
-// 65,536-cell developed flame 0.526 -> 0.416 ms, 65,536-cell mixing layer 27.6 -> 10.6 ms.
+// 65,536-cell developed flame 0.526 -> 0.405 ms, 65,536-cell mixing layer 27.6 -> 10.6 ms.
 // Every scalar that steers control flow is the same in all 64 lanes (butterfly sums), so a wave
 // never diverges.
 #include <cmath>
@@ -86,7 +86,7 @@ __global__ __launch_bounds__(64 * kQueueWaves) void chem_cell_kernel(CellMech mg
     // cells, another place in each run, so that a hot column of a field meets every block, and its waves
     // share them out through a counter in LDS.  One wave per cell for any number of cells, whose start (its rows of
     // the mechanism) a one-sub-step cell pays a sixth of its time for: flame of 8,000 cells 75 us, 65,536 cells
-    // 522 us, this way 60 and 394 us (16 lanes 65 and 476); hot-kernel field of 65,536 cells 5.4 and 3.5 ms (10.3).
+    // 522 us, this way 58 and 387 us (16 lanes 65 and 476); hot-kernel field of 65,536 cells 5.4 and 3.5 ms (10.3).
     const bool local = !queue && waves > 1;
     int64_t at = TAPE ? cell_of_block(a.n) : int64_t(blockIdx.x);  // place of the wave's cell
     auto local_place = [&]() {
@@ -120,7 +120,8 @@ __global__ __launch_bounds__(64 * kQueueWaves) void chem_cell_kernel(CellMech mg
     if (lane == 0) sh[C::oC] = 1.0;
     lds_order();
     // The arguments, read from the kernel's argument segment where they are used: held in registers, they would push
-    // what every attempt needs out of them.
+    // what every attempt needs out of them, some of it to scratch memory, which an empty launch pays for too (the
+    // fallback of a DNN step on one cell: 0.7 of its 34 us).
     typedef const __attribute__((address_space(4))) StepArgs *ArgPtr;
     const auto seg = (const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr();
     auto args = [&]() {
@@ -128,23 +129,29 @@ __global__ __launch_bounds__(64 * kQueueWaves) void chem_cell_kernel(CellMech mg
         asm volatile("" : "+s"(p));
         return p;
     };
-    const double atol = (r == 0) ? a.o.atol_T : a.o.atol_Y;
+    auto atol = [&](ArgPtr b) { return (r == 0) ? b->o.atol_T : b->o.atol_Y; };
     const int32_t *order = queue ? q.order : q.cidx;
-    double *const yp = (r == 0) ? a.T : a.Y + int64_t(r <= K ? r - 1 : 0) * a.ld;  // the lane's row
-    double *const rrp = a.rr ? a.rr + int64_t(r >= 1 && r <= K ? r - 1 : 0) * a.ld : nullptr;
+    // the lane's row of T and Y, or of rr, at a cell
+    const unsigned row = r >= 1 && r <= K ? r - 1 : 0;
+    auto row_of = [&](ArgPtr b, int64_t cell) { return r == 0 ? b->T + cell : b->Y + (row * b->ld + cell); };
+    auto rr_of = [&](ArgPtr b, int64_t cell) { return b->rr + (row * b->ld + cell); };
     // A place's cell and the cell's state.  (Loads by an index that the compiler takes for different in each lane:
     // a scalar load would be waited for by the next LDS access.)
-    int zero = 0;
-    asm("" : "+v"(zero));
-    auto cell_at = [&](int64_t place) { return order ? order[place + zero] : int32_t(place); };
+    auto vector_zero = []() {
+        int z = 0;
+        asm("" : "+v"(z));
+        return z;
+    };
+    auto cell_at = [&](int64_t place) { return order ? order[place + vector_zero()] : int32_t(place); };
     int64_t i = 0;
     double yn = 0.0, pn = 0.0, dtn = 0.0;
     auto fetch = [&](int32_t cell) {
         const auto b = args();
         i = int64_t(__builtin_amdgcn_readfirstlane(cell));
-        if (r < N) yn = yp[i];
-        pn = b->p[i + zero];
-        dtn = b->dts ? b->dts[i + zero] : b->dt;
+        if (r < N) yn = *row_of(b, i);
+        const int64_t iv = i + vector_zero();
+        pn = b->p[iv];
+        dtn = b->dts ? b->dts[iv] : b->dt;
     };
     auto claim = [&]() {
         unsigned long long old = 0;
@@ -175,7 +182,7 @@ __global__ __launch_bounds__(64 * kQueueWaves) void chem_cell_kernel(CellMech mg
         // The cell that follows is claimed when an attempt starts that would end this one, and its index and
         // state are loaded while that attempt's stages run; a chain that goes on holds no other cell back.  With a
         // claim after each single cell, and four cells per claim in the order's colder part, small flames waited for
-        // them (24,000 cells 212 us, now 173; 16 lanes 202) and uniformly stiff fields for the last units (32,768
+        // them (24,000 cells 212 us, now 171; 16 lanes 202) and uniformly stiff fields for the last units (32,768
         // ignition cells 22.4 ms, now 17.1).
         enum { kNone, kClaimed, kIndexed, kLoaded, kEmpty };
         int ahead = kNone;
@@ -200,7 +207,7 @@ __global__ __launch_bounds__(64 * kQueueWaves) void chem_cell_kernel(CellMech mg
                     }
                     if (TAPE) Tape(K, b->n, b->tape_cap).count(b->tape)[ic] = -1;
                 }
-                if (b->rr && lane >= 1 && lane <= K) rrp[ic] = 0.0;
+                if (b->rr && lane >= 1 && lane <= K) *rr_of(b, ic) = double(vector_zero());
                 if ((at = next(false)) < 0) return;
                 fetch(cell_at(at));
                 continue;
@@ -209,16 +216,11 @@ __global__ __launch_bounds__(64 * kQueueWaves) void chem_cell_kernel(CellMech mg
             c.c6p = c.p * (1e-6 / kR);
             c.lc6p = dlogp(kc, c.c6p);
             const double y0 = yr;
-            double rho0 = 0.0;
-            if (b->rr) {  // input density over dt, for rr
-                const double sYW = row_sum((r == 0) ? 0.0 : yr * o.iW);
-                rho0 = fdiv(c.p, sYW * kR * lane_value(yr, 0) * dtc);
-            }
             const double h_in = b->h_io ? b->h_io[ic] : 0.0;
             bool fresh = !(h_in > 0.0);
             double h = fresh ? 0.0 : fmin(h_in, dtc);
             if (!fresh && !(h >= b->o.h_min)) h = b->o.h_min;
-            double t = 0.0, h_final = 0.0;
+            double t = 0.0;
             int acc = 0, rej = 0;
             bool prev_rej = false;
             int st;
@@ -232,7 +234,7 @@ __global__ __launch_bounds__(64 * kQueueWaves) void chem_cell_kernel(CellMech mg
                 const double f0 = C::jacobian(mg, kc, o, c, sh, lane, r, g, yr, w);
                 if (fresh) {
                     // initial sub-step from the weighted norms of y0 and f(y0)
-                    const double isc = frcp(atol + e->o.rtol * fabs(yr));
+                    const double isc = frcp(atol(e) + e->o.rtol * fabs(yr));
                     const double qy = (r < N) ? yr * isc : 0.0, qf = (r < N) ? f0 * isc : 0.0;
                     const double ny = lane_value(row_sum(qy * qy), 0), nf = lane_value(row_sum(qf * qf), 0);
                     h = (nf > 0.0) ? fmin(0.01 * sqrt(ny / nf), dtc) : dtc;
@@ -283,7 +285,7 @@ __global__ __launch_bounds__(64 * kQueueWaves) void chem_cell_kernel(CellMech mg
                 }
                 // y_new = (stage-6 state) + u6 ; error = u6
                 const double ynr = ysr + u[5];
-                const double sc = atol + e->o.rtol * fmax(fabs(yr), fabs(ynr));
+                const double sc = atol(e) + e->o.rtol * fmax(fabs(yr), fabs(ynr));
                 const double er = (r < N) ? u[5] * frcp3(sc) : 0.0;
                 const double e2 = lane_value(row_sum(er * er) * (1.0 / N), 0);  // squared norm
                 const double fmx = prev_rej ? 1.0 : 6.0;
@@ -318,7 +320,6 @@ __global__ __launch_bounds__(64 * kQueueWaves) void chem_cell_kernel(CellMech mg
                     }
                     ++acc;
                     yr = (r < N) ? ynr : 0.0;
-                    h_final = h;
                     prev_rej = false;
                     if (last) {
                         st = DF_CELL_OK;
@@ -347,16 +348,19 @@ __global__ __launch_bounds__(64 * kQueueWaves) void chem_cell_kernel(CellMech mg
                 if (st == DF_CELL_OK && acc > e->tape_cap) st = DF_CELL_TAPE_FULL;
                 if (lane == 0) Tape(K, e->n, e->tape_cap).count(e->tape)[ic] = (st == DF_CELL_OK) ? acc : -1;
             }
-            if (lane < N) yp[ic] = yr;
+            if (lane < N) *row_of(e, ic) = yr;
+            if (e->rr) {  // rr = rho0 (Y - Y0) / dt with the input state's density rho0
+                const double sYW = row_sum((r == 0) ? 0.0 : y0 * o.iW);
+                const double rho0 = fdiv(1e6 * c.c6p, sYW * lane_value(y0, 0) * dtc);
+                if (lane >= 1 && lane <= K) *rr_of(e, ic) = rho0 * (yr - y0);
+            }
             if (lane == 0) {
-                if (e->h_io) e->h_io[ic] = (st == DF_CELL_OK) ? h_final : h;
+                if (e->h_io) e->h_io[ic] = h;  // (an accepted sub-step that ended the cell left it as it was)
                 if (e->status) e->status[ic] = (st == DF_CELL_OK) ? e->status_ok : st;
                 if (e->nsteps) {
                     e->nsteps[ic] = acc;
                     e->nsteps[e->n + ic] = rej;
                 }
-            } else if (lane <= K && e->rr) {
-                rrp[ic] = rho0 * (yr - y0);
             }
         }
         if (ahead == kLoaded) continue;
