@@ -172,7 +172,9 @@ __global__ __launch_bounds__(64 * kQueueWaves) void chem_cell_kernel(CellMech mg
                 if (left-- == 0) return int64_t(-1);
                 grp.group(q.ctr, limit, (grp.s + 1) % kCellQueues, waves);
                 const unsigned long long c = __hip_atomic_load(grp.ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if (int64_t(c & 0xffffffffull) + int64_t(c >> 32) + grp.fw + grp.bw < grp.n) break;
+                const int64_t taken_front = unsigned(__builtin_amdgcn_readfirstlane(int(c)));
+                const int64_t taken_back = unsigned(__builtin_amdgcn_readfirstlane(int(c >> 32)));
+                if (taken_front + taken_back + grp.fw + grp.bw < grp.n) break;
             }
         }
     };
