@@ -23,7 +23,7 @@
 //     permutation), so a stage solve is three products and two lane swaps per lane.
 // Measured on MI355X: an attempt of a lone wave takes 17k cycles (47k with 16 lanes per cell, whose wave issues
 // 9,000 instructions for four cells); with two waves per SIMD a SIMD finishes one every 12k, its vector unit busy
-// 84 % of the time with 2,180 vector instructions per attempt (77 % and 2,410 per one-sub-step cell, its start and end
+// 84 % of the time with 2,190 vector instructions per attempt (79 % and 2,430 per one-sub-step cell, its start and end
 // included).  Whole calls with a workspace, 16 lanes -> this kernel: 21 ignition cells 2.98 -> 1.21 ms, 1,001 cells
 // 3.40 -> 1.37 ms, 32,768 cells 19.5 -> 17.1 ms (the 16-lane queue 17.9), 65,536-cell hot-kernel field 4.97 -> 2.58 ms,
 // 65,536-cell developed flame 0.526 -> 0.405 ms, 65,536-cell mixing layer 27.6 -> 10.6 ms.
